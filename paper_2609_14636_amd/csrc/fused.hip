@@ -37,8 +37,9 @@
 //   super-rows at d = 2,048) and a band is walked one super-column at a time:
 //   the band's H and the current W slab both stay in the 256 MB last-level
 //   cache, so each W slab comes from HBM once per band instead of once per
-//   super-row.  With fewer than 16 (or 8) row tiles the super-tile is 8 x 32
-//   (or 4 x 64) tiles, so every XCD still has tiles.
+//   super-row.  Row tiles and vocabulary tiles past the last whole super-tile
+//   are numbered apart, without holes (tile_of), so that every XCD and every
+//   shader engine of it has the same share of them.
 // Kernel 2: z_y = h . w_y per row (one wave per row, fp32).
 // Kernel 3: four waves per 64 rows merge each row's V/128 partials (reads
 //   coalesced across rows) and write log pi_T(y) = (z_y - m) - log s.
@@ -79,9 +80,8 @@ struct FusedArgs {
     int32_t vocab;
     int32_t d;
     int32_t n_half;
-    int32_t tiles_m, tiles_n, super_rows, super_cols;
-    int32_t xcd_cols;      // XCD blocks per super-tile row: 2, 4 or 8 (the super-tile is
-                           // 32 / xcd_cols row tiles by 8 * xcd_cols vocabulary tiles)
+    int32_t tiles_m, tiles_n;
+    int32_t super_rows, super_cols;  // whole super-tiles of 16 x 16 tiles along rows and vocabulary
     int32_t band;          // super-rows per band; a band is walked one super-column at a time
 };
 
@@ -115,6 +115,56 @@ __device__ __forceinline__ void barrier() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// Tile (row tile tm, vocabulary tile tn) of workgroup b.  Three regions, one after the other:
+//   A  whole super-tiles, 256 workgroups each, in bands of super-rows;
+//   B  the vocabulary tiles past the last whole super-column, for the rows of region A: each XCD
+//      takes an eighth of the row tiles;
+//   C  the row tiles past the last whole super-row (up to 15), for every vocabulary tile, in
+//      one strip of up to 8 row tiles or two: XCD x takes the vocabulary tiles x, x + 8, ... and
+//      all the strip's rows of each in turn.
+// Every number in A and B is a tile, and in C all but the last vocabulary tiles' of some XCDs.
+// Holes cost more than their own empty workgroups: an XCD hands consecutive workgroups to its
+// four shader engines in turn, so numbering a single row tile as the first of a block of four
+// left three quarters of the chip idle.  Measured with V = 151,936, d = 2,048: 431 us for 64 to
+// 512 rows with such holes, 213 to 280 us without; 5,000 rows 3.56 ms against 2.19 ms.
+__host__ __device__ inline int strip_rows(int rem) { return rem > 8 ? (rem + 1) / 2 : rem; }
+
+__device__ __forceinline__ void tile_of(const FusedArgs &a, int b, int &tm, int &tn) {
+    const int xcd = b & 7;
+    int s = b >> 3;
+    const int n_a = a.super_rows * a.super_cols * 32;  // per XCD
+    if (s < n_a) {
+        const int S = s >> 5, q = s & 31;
+        // super-tile S -> (super-row, super-column): bands of a.band super-rows, each band
+        // walked column by column, so a W slab read from HBM serves the whole band from the
+        // last-level cache while the band's H stays there too
+        const int per_band = a.band * a.super_cols;
+        const int bi = S / per_band, r0 = bi * a.band, idx = S - bi * per_band;
+        const int rows_b = (a.super_rows - r0) < a.band ? (a.super_rows - r0) : a.band;
+        tm = (r0 + idx % rows_b) * 16 + (xcd >> 1) * 4 + (q & 3);
+        tn = (idx / rows_b) * 16 + (xcd & 1) * 8 + (q >> 2);
+        return;
+    }
+    s -= n_a;
+    const int cols = a.tiles_n - a.super_cols * 16, n_b = a.super_rows * 2 * cols;
+    if (s < n_b) {
+        tm = xcd * a.super_rows * 2 + s / cols;
+        tn = a.super_cols * 16 + s % cols;
+        return;
+    }
+    s -= n_b;
+    const int per_xcd = (a.tiles_n + 7) >> 3;
+    tm = a.super_rows * 16;
+    int h = strip_rows(a.tiles_m - tm);
+    if (s >= h * per_xcd) {
+        s -= h * per_xcd;
+        tm += h;
+        h = a.tiles_m - tm;
+    }
+    tm += s % h;
+    tn = (s / h) * 8 + xcd;
+}
+
 __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -124,19 +174,8 @@ __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
     const int wv = wave & 1, wt = wave >> 1;     // vocabulary half, token quarter
 
     // ---- tile of this workgroup (XCD-aware order) ----
-    const int b = blockIdx.x;
-    const int xcd = b & 7, s = b >> 3;
-    const int S = s >> 5, q = s & 31;
-    const int xc = a.xcd_cols, xr = 8 / xc;
-    // super-tile S -> (super-row, super-column): bands of a.band super-rows, each band
-    // walked column by column, so a W slab read from HBM serves the whole band from the
-    // last-level cache while the band's H stays there too
-    const int per_band = a.band * a.super_cols;
-    const int bi = S / per_band, r0 = bi * a.band, idx = S - bi * per_band;
-    const int rows_b = (a.super_rows - r0) < a.band ? (a.super_rows - r0) : a.band;
-    const int sr = r0 + idx % rows_b, sc = idx / rows_b;
-    const int tm = sr * (4 * xr) + (xcd / xc) * 4 + (q & 3);
-    const int tn = sc * (8 * xc) + (xcd % xc) * 8 + (q >> 2);
+    int tm, tn;
+    tile_of(a, (int)blockIdx.x, tm, tn);
     if (tm >= a.tiles_m || tn >= a.tiles_n) return;
     const int64_t m0 = (int64_t)tm * kBM;
     const int64_t n0 = (int64_t)tn * kBN;
@@ -440,25 +479,24 @@ hipError_t launch_fused_teacher(const uint16_t *h, const uint16_t *w, const int3
     a.n_half = (vocab + kHalf - 1) / kHalf;
     a.tiles_m = (int)((n_rows + kBM - 1) / kBM);
     a.tiles_n = (vocab + kBN - 1) / kBN;
-    // Few row tiles (small batches): lay the eight XCD blocks out along V instead, so
-    // every XCD still gets work.
-    a.xcd_cols = a.tiles_m >= 16 ? 2 : (a.tiles_m >= 8 ? 4 : 8);
-    const int xr = 8 / a.xcd_cols;
-    a.super_cols = (a.tiles_n + 8 * a.xcd_cols - 1) / (8 * a.xcd_cols);
-    const int super_rows = (a.tiles_m + 4 * xr - 1) / (4 * xr);
-    a.super_rows = super_rows;
-    const int64_t h_super_row = (int64_t)4 * xr * kBM * d * 2;  // H bytes of one super-row
+    a.super_rows = a.tiles_m / 16;
+    a.super_cols = a.tiles_n / 16;
+    const int64_t h_super_row = (int64_t)16 * kBM * d * 2;  // H bytes of one super-row
     int64_t band = kBandHBytes / h_super_row;
 #ifdef STRIDE_FUSED_BAND_HOOK
     if (const int32_t o = g_band_override.load()) band = o;
 #endif
-    a.band = (int)(band < 1 ? 1 : (band > super_rows ? super_rows : band));
+    if (band > a.super_rows) band = a.super_rows;
+    a.band = (int)(band < 1 ? 1 : band);
     a.partial = static_cast<float2 *>(ws);
     float *zy = reinterpret_cast<float *>(static_cast<char *>(ws) +
                                           (size_t)a.n_half * n_rows * sizeof(float2));
     hipError_t e = ensure_lds_limit();
     if (e != hipSuccess) return e;
-    const int64_t blocks = (int64_t)super_rows * a.super_cols * 256;
+    const int64_t rem = a.tiles_m - a.super_rows * 16;
+    const int64_t blocks = 8 * ((int64_t)a.super_rows * a.super_cols * 32 +
+                                (int64_t)a.super_rows * 2 * (a.tiles_n - a.super_cols * 16) +
+                                rem * ((a.tiles_n + 7) / 8));
     if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;  // grid past the 32-bit limit
     hipLaunchKernelGGL(fused_lse_kernel, dim3((unsigned)blocks), dim3(kThreads), kLdsBytes, stream, a);
     e = hipGetLastError();

@@ -61,6 +61,35 @@ def test_fused_parity(R, turns, tok, vocab, d):
     say(f"[fused] {_fused_vs_oracle(wl)}")
 
 
+@pytest.mark.parametrize("rows,vocab", [
+    (512, 4400),     # two row tiles, 18 vocabulary tiles: one strip, XCDs with 2 and 3 of them
+    (2049, 1800),    # 9 row tiles: strips of 5 and 4; 8 vocabulary tiles, one per XCD
+    (3840, 257),     # 15 row tiles: strips of 8 and 7; two vocabulary tiles, six XCDs without one
+    (4096, 3840),    # one super-row, no whole super-column: only the columns' region
+    (4352, 4096),    # 17 row tiles, 16 vocabulary tiles: no leftover column
+    (6400, 8449),    # 25 row tiles, 34 vocabulary tiles: all three regions, strips of 5 and 4
+])
+def test_fused_tile_numbering(rows, vocab):
+    """Row and vocabulary tiles past the last whole 16 x 16 super-tile are numbered apart; the
+    partial table is filled with NaN first, so a tile that no workgroup takes shows in its rows.
+    The first and last row of every row tile against the oracle."""
+    import torch
+    import paper_2609_14636_amd as P
+    wl = W.make("fused", seed=5 + rows, scale=dict(R=1, turns=1, tok=rows, vocab=vocab, d=64))
+    inp = H.device_inputs_fused(wl)
+    path = P.Path(inp["layout"], wl.unit, with_student=False, fused_vocab=vocab)
+    path.fused_ws.fill_(0xFF)
+    path.score_fused(vocab, inp["hidden"], inp["w"], None, inp["ids"])
+    torch.cuda.synchronize()
+    assert int(path.flags.item()) == 0
+    got = path.logp_t.cpu().numpy()
+    assert np.isfinite(got).all()
+    at = np.unique(np.minimum(np.concatenate([np.arange(0, rows, 256), np.arange(255, rows + 255, 256)]),
+                              rows - 1))
+    sc, _ = H.oracle_fused_scores(wl, at)
+    assert np.max(np.abs(got[at] - sc["logp_t"])) <= H.TOL_LOGP
+
+
 def test_fused_random_shapes():
     """Thirty random small shapes against the oracle: 1 to 1,200 rows (partial row tiles),
     vocabularies of 1 to 5,000 entries (partial 128- and 256-column tiles) and hidden sizes of one
