@@ -40,9 +40,8 @@
 //   super-row.  Row tiles and vocabulary tiles past the last whole super-tile
 //   are numbered apart, without holes (tile_of), so that every XCD and every
 //   shader engine of it has the same share of them.
-// Kernel 2: z_y = h . w_y per row (one wave per row, fp32).
-// Kernel 3: four waves per 64 rows merge each row's V/128 partials (reads
-//   coalesced across rows) and write log pi_T(y) = (z_y - m) - log s.
+// Kernel 2: z_y = h . w_y per row (one wave per row, fp32), the merge of each row's V/128
+//   partials, and log pi_T(y) = (z_y - m) - log s.
 #include <atomic>
 
 #include "common.hpp"
@@ -349,34 +348,6 @@ __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
     }
 }
 
-// z_y = h . w_y, one wave per row, fp32.
-__global__ __launch_bounds__(256) void fused_gather_kernel(const uint16_t *h, const uint16_t *w,
-                                                           const int32_t *ids, float *zy,
-                                                           int64_t n_rows, int32_t vocab, int32_t d) {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= n_rows) return;
-    const int32_t y = ids[row];
-    if (y < 0 || y >= vocab) {
-        if (lane == 0) zy[row] = __builtin_nanf("");
-        return;
-    }
-    const u32x4 *hp = reinterpret_cast<const u32x4 *>(h + row * d);
-    const u32x4 *wp = reinterpret_cast<const u32x4 *>(w + (int64_t)y * d);
-    float acc = 0.0f;
-    for (int c = lane; c < d / 8; c += 64) {
-        const u32x4 x = hp[c], z = wp[c];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc = __builtin_fmaf(__uint_as_float(x[e] << 16), __uint_as_float(z[e] << 16), acc);
-            acc = __builtin_fmaf(__uint_as_float(x[e] & 0xFFFF0000u), __uint_as_float(z[e] & 0xFFFF0000u), acc);
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) zy[row] = acc;
-}
-
 // Fold one partial (max p.x, sum p.y of exp(z - p.x)) into a running (m, s).
 __device__ __forceinline__ void fold_partial(float &m, float &s, const float2 p) {
     const float mn = fmaxf(m, p.x);
@@ -385,44 +356,91 @@ __device__ __forceinline__ void fold_partial(float &m, float &s, const float2 p)
     m = mn;
 }
 
-constexpr int kMergeRows = 64;   // rows per workgroup, one per lane
-constexpr int kMergeSplit = 4;   // waves per workgroup, each folding every 4th partial
+constexpr int kMergeThreads = 1024;  // 16 waves per workgroup
+// Rows from which a merge workgroup takes 64 rows instead of 16: measured, 16 rows take 30.1 us
+// against 33.0 at 8,192 rows and 52.0 against 46.8 at 16,384, where every CU has its workgroups
+// either way and the longer runs of consecutive rows count.
+constexpr int64_t kMergeWide = 12288;
 
-// Merge the V/128 partials of each row and finish log pi_T(y).  Wave w of a workgroup
-// folds partials w, w+4, w+8, ... of its 64 rows (each load is 64 consecutive rows,
-// 512 contiguous bytes, eight loads in flight); the four wave results are combined in
-// LDS in wave order, so the result does not depend on timing.
-__global__ __launch_bounds__(256) void fused_merge_kernel(const float2 *partial, const float *zy,
-                                                          const int32_t *ids, float *logp_t,
-                                                          int64_t n_rows, int32_t n_half,
-                                                          int32_t vocab, uint32_t *flags) {
-    __shared__ float2 red[kMergeSplit][kMergeRows];
-    const int r = threadIdx.x & (kMergeRows - 1), sp = threadIdx.x / kMergeRows;
-    const int64_t row = (int64_t)blockIdx.x * kMergeRows + r;
+// z_y = h . w_y and the merge of the row's V/128 partials, RW rows per workgroup.  Wave v takes
+// the dot products of rows v, v + 16, ... (fp32, one row at a time over all its lanes).  Thread
+// (sp, r) folds partials sp, sp + 1024/RW, ... of row r, eight loads in flight, each load
+// instruction reading runs of RW consecutive rows (8 RW contiguous bytes); the threads of a row
+// are combined by lane exchanges and then through LDS, always in the same order, so the result
+// does not depend on timing.
+// Latency bounds it while the workgroups are few: at RW = 16 a thread's chain is 1,187 / 64
+// folds.  Measured (V = 151,936, d = 2,048) against a merge of four waves per 64 rows (chains
+// of 1,187 / 4) after a kernel of its own for z_y: 64 rows 29.3 -> 9.8 us, 4,096 rows 35.7 ->
+// 14.7, 16,384 rows 55.5 -> 46.8, 65,536 rows 193 -> 186.
+template <int RW>
+__global__ __launch_bounds__(kMergeThreads) void fused_merge_kernel(
+    const float2 *__restrict__ partial, const uint16_t *__restrict__ h,
+    const uint16_t *__restrict__ w, const int32_t *__restrict__ ids, float *__restrict__ logp_t,
+    int64_t n_rows, int32_t n_half, int32_t vocab, int32_t d, uint32_t *flags) {
+    constexpr int kWaves = kMergeThreads / kWave, kSplit = kMergeThreads / RW;
+    __shared__ float2 red[kWaves][RW];
+    __shared__ float s_zy[RW];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int r = threadIdx.x & (RW - 1), sp = threadIdx.x / RW;
+    const int64_t row0 = (int64_t)blockIdx.x * RW, row = row0 + r;
+#pragma unroll
+    for (int q = wave; q < RW; q += kWaves) {
+        if (row0 + q >= n_rows) break;
+        const int32_t y = ids[row0 + q];
+        float acc = __builtin_nanf("");
+        if (y >= 0 && y < vocab) {
+            acc = 0.0f;
+            const u32x4 *hp = reinterpret_cast<const u32x4 *>(h + (row0 + q) * d);
+            const u32x4 *wp = reinterpret_cast<const u32x4 *>(w + (int64_t)y * d);
+            for (int c = lane; c < d / 8; c += kWave) {
+                const u32x4 x = hp[c], z = wp[c];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc = __builtin_fmaf(__uint_as_float(x[e] << 16), __uint_as_float(z[e] << 16), acc);
+                    acc = __builtin_fmaf(__uint_as_float(x[e] & 0xFFFF0000u),
+                                         __uint_as_float(z[e] & 0xFFFF0000u), acc);
+                }
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
+        }
+        if (lane == 0) s_zy[q] = acc;
+    }
     float m = -INFINITY, s = 0.0f;
     if (row < n_rows) {
         const float2 *col = partial + row;
         int j = sp;
         constexpr int U = 8;
-        for (; j + (U - 1) * kMergeSplit < n_half; j += U * kMergeSplit) {
+        for (; j + (U - 1) * kSplit < n_half; j += U * kSplit) {
             float2 p[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) p[u] = col[(int64_t)(j + u * kMergeSplit) * n_rows];
+            for (int u = 0; u < U; ++u) p[u] = col[(int64_t)(j + u * kSplit) * n_rows];
 #pragma unroll
             for (int u = 0; u < U; ++u) fold_partial(m, s, p[u]);
         }
-        for (; j < n_half; j += kMergeSplit) fold_partial(m, s, col[(int64_t)j * n_rows]);
-    }
-    red[sp][r] = make_float2(m, s);
-    __syncthreads();
-    if (sp != 0 || row >= n_rows) return;
+        float2 p[U];
 #pragma unroll
-    for (int k = 1; k < kMergeSplit; ++k) fold_partial(m, s, red[k][r]);
+        for (int u = 0; u < U; ++u)
+            p[u] = j + u * kSplit < n_half ? col[(int64_t)(j + u * kSplit) * n_rows]
+                                           : make_float2(-INFINITY, 0.0f);
+#pragma unroll
+        for (int u = 0; u < U; ++u) fold_partial(m, s, p[u]);
+    }
+#pragma unroll
+    for (int off = RW; off < kWave; off <<= 1) {
+        const float m2 = __shfl_xor(m, off, kWave), s2 = __shfl_xor(s, off, kWave);
+        fold_partial(m, s, make_float2(m2, s2));
+    }
+    if (lane < RW) red[wave][lane] = make_float2(m, s);
+    __syncthreads();
+    if (threadIdx.x >= RW || row >= n_rows) return;
+#pragma unroll
+    for (int k = 1; k < kWaves; ++k) fold_partial(m, s, red[k][r]);
     const int32_t y = ids[row];
     uint32_t bad = 0;
     if (!((m > -INFINITY) && (m < INFINITY) && (s > 0.0f) && (s < INFINITY))) bad |= STRIDE_FLAG_NONFINITE;
     if (y < 0 || y >= vocab) bad |= STRIDE_FLAG_TOKEN_OOB;
-    const float z = zy[row];
+    const float z = s_zy[r];
     if (!bad && !(z > -INFINITY && z < INFINITY)) bad |= STRIDE_FLAG_NONFINITE;
     if (bad) {
         raise_flag(flags, bad);
@@ -463,6 +481,7 @@ hipError_t ensure_lds_limit() {
 
 size_t fused_ws_bytes(int64_t n_rows, int32_t vocab) {
     const int64_t n_half = ((int64_t)vocab + kHalf - 1) / kHalf;
+    // the partial table; the floats after it are spare (the size stays what callers were given)
     return (size_t)n_half * n_rows * sizeof(float2) + (size_t)n_rows * sizeof(float) + 256;
 }
 
@@ -489,8 +508,6 @@ hipError_t launch_fused_teacher(const uint16_t *h, const uint16_t *w, const int3
     if (band > a.super_rows) band = a.super_rows;
     a.band = (int)(band < 1 ? 1 : band);
     a.partial = static_cast<float2 *>(ws);
-    float *zy = reinterpret_cast<float *>(static_cast<char *>(ws) +
-                                          (size_t)a.n_half * n_rows * sizeof(float2));
     hipError_t e = ensure_lds_limit();
     if (e != hipSuccess) return e;
     const int64_t rem = a.tiles_m - a.super_rows * 16;
@@ -501,13 +518,10 @@ hipError_t launch_fused_teacher(const uint16_t *h, const uint16_t *w, const int3
     hipLaunchKernelGGL(fused_lse_kernel, dim3((unsigned)blocks), dim3(kThreads), kLdsBytes, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fused_gather_kernel, dim3((unsigned)((n_rows + 3) / 4)), dim3(256), 0, stream,
-                       h, w, ids, zy, n_rows, vocab, d);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fused_merge_kernel, dim3((unsigned)((n_rows + kMergeRows - 1) / kMergeRows)),
-                       dim3(kMergeRows * kMergeSplit), 0,
-                       stream, a.partial, zy, ids, logp_t, n_rows, a.n_half, vocab, flags);
+    const int rw = n_rows < kMergeWide ? 16 : 64;
+    hipLaunchKernelGGL(n_rows < kMergeWide ? fused_merge_kernel<16> : fused_merge_kernel<64>,
+                       dim3((unsigned)((n_rows + rw - 1) / rw)), dim3(kMergeThreads), 0, stream,
+                       a.partial, h, w, ids, logp_t, n_rows, a.n_half, vocab, d, flags);
     return hipGetLastError();
 }
 

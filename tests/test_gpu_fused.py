@@ -67,6 +67,7 @@ def test_fused_parity(R, turns, tok, vocab, d):
     (3840, 257),     # 15 row tiles: strips of 8 and 7; two vocabulary tiles, six XCDs without one
     (4096, 3840),    # one super-row, no whole super-column: only the columns' region
     (4352, 4096),    # 17 row tiles, 16 vocabulary tiles: no leftover column
+    (12301, 300),    # from 12,288 rows on the merge takes 64 rows per workgroup; 13 in the last
     (6400, 8449),    # 25 row tiles, 34 vocabulary tiles: all three regions, strips of 5 and 4
 ])
 def test_fused_tile_numbering(rows, vocab):
