@@ -349,7 +349,8 @@ stride_status stride_probe_copy(const void *src, void *dst, const uint8_t *row_m
 /* Test hook of the stop test's cross-workgroup look-back (not a step of the method).
  *
  * In the library built for testing (libstride_debug.so, scan compiled with
- * STRIDE_SCAN_DELAY_HOOK), later stride_stop / stride_stop_noalloc calls make the scan tiles
+ * STRIDE_SCAN_DELAY_HOOK), later stride_stop / stride_stop_noalloc calls that scan tiles (more
+ * than 2^19 units, or 2^15 per rollout on average) make those
  * picked by a hash of (seed, tile) -- about one in `one_in` -- sleep 1 .. `sleeps` times
  * s_sleep(127) (about 8,000 cycles each) before publishing their aggregate, so that their
  * successors look back over descriptors that are not yet published.  The waits stay far below
@@ -362,7 +363,7 @@ stride_status stride_debug_scan_delay(uint64_t seed, uint32_t one_in, uint32_t s
 /* Test hook of the look-back's bounded wait (not a step of the method).
  *
  * In libstride_debug.so, later stride_stop / stride_stop_noalloc calls let a scan tile wait at
- * most `limit` rounds of s_sleep(1) for each predecessor's descriptor instead of the library's
+ * most `limit` rounds of s_sleep(1) for its predecessors' descriptors instead of the library's
  * own bound (2^22 rounds); limit = 0 restores that bound.  With a tiny limit and the delays of
  * stride_debug_scan_delay, successors give up: the call still completes, raises
  * STRIDE_FLAG_SPIN_LIMIT and writes NaN to the cumulative values that needed the missing carry,

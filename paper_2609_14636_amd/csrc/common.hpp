@@ -23,11 +23,11 @@ struct PtrTable {
     const void *p[STRIDE_MAX_DOMAINS];
 };
 
-// Scan tile descriptor published by one tile and read by its successors.
+// Scan tile descriptor published by one tile and read by its successors: the sum of the tile's
+// values after its last segment head, one half in the upper 32 bits of each word; the lower 32
+// bits of each are 0 until published, then bit 0 set, and bit 1 if a segment starts in the tile.
 struct alignas(16) TileDesc {
-    double value;     // sum of the tile's values after its last segment head
-    uint32_t head;    // 1 if a segment starts inside the tile
-    uint32_t status;  // 0 = not yet published, 1 = aggregate ready
+    uint64_t hi, lo;
 };
 
 // Workspace layout (byte offsets from ws, each region 256-byte aligned).

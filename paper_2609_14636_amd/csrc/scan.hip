@@ -15,13 +15,14 @@
 //      (per-thread sequential, then a fixed shuffle tree, then waves in order),
 //      with the segmented operator (f1,v1)+(f2,v2) = (f1|f2, f2 ? v2 : v1+v2).
 //   3. It publishes its aggregate (value after its last rollout start, and
-//      whether one occurs) with a release store, before waiting on anything.
+//      whether one occurs) in two self-contained words, before waiting on anything.
 //   4. If its first unit continues a rollout, it looks back over predecessor
-//      aggregates only, nearest first, until the tile holding that rollout's
-//      start.  Inclusive prefixes are never used, so every sum is associated
-//      in the same order on every run: cum is bit-reproducible.
+//      aggregates only, 64 at a time, added nearest first, until the tile holding
+//      that rollout's start.  Inclusive prefixes are never used, so every sum is
+//      associated in the same order on every run: cum is bit-reproducible.
 //   5. The first crossing per rollout is an integer min, reduced in LDS and
 //      then with one global atomicMin per rollout per tile.
+// A call of one tile needs none of this and runs as one workgroup in one launch.
 // Waits are bounded: past the spin limit the tile gives up, raises
 // STRIDE_FLAG_SPIN_LIMIT and writes NaN, so no wave can hang.
 #include <atomic>
@@ -33,7 +34,16 @@
 namespace stride {
 namespace {
 
-constexpr int kSlots = 256;            // rollouts per tile reduced in LDS
+constexpr int kSlots = 256;            // rollouts per tile held in LDS
+// Units of the call, and of its average rollout, up to which each rollout gets a group of threads
+// of its own (stop_rollout_kernel, one launch) instead of the tiles' three launches.  The whole
+// test, tiles -> groups: 8 x 8 units 17.7 -> 3.6 us, 2,000 x 12 24.2 -> 4.7, 64 x 4,096 25.6 ->
+// 7.3, 2 x 30,000 23.4 -> 15.9.  A group scans its rollout alone, about 3 us for every 8,192
+// units, where tiles spread it over the chip: one rollout of 172,000 units takes 61.6 us as a
+// group and 20.4 as tiles, one of 516,000 196 and 29.5.  The host does not know the longest
+// rollout, so the call's own limit bounds what one long rollout among short ones can cost.
+constexpr int64_t kRolloutUnits = 1 << 19;
+constexpr int64_t kRolloutLength = 1 << 15;
 constexpr uint32_t kSpinLimit = 1u << 22;
 
 struct StopArgs {
@@ -70,29 +80,6 @@ std::atomic<uint32_t> g_delay_sleeps{0};
 std::atomic<uint32_t> g_spin_limit{0};
 #endif
 
-// unit_off, stop_unit sentinels, descriptor reset, tile counter reset.
-__global__ __launch_bounds__(256) void stop_prep_kernel(StopArgs a, int64_t *unit_off) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t R = a.L.n_rollouts, T = a.L.n_turns;
-    if (i <= R) {
-        int64_t t = a.L.rollout_turn_off[i];
-        bool bad = t < 0 || t > T;
-        if (i == 0 && t != 0) bad = true;
-        if (i == R && t != T) bad = true;
-        if (i < R && a.L.rollout_turn_off[i + 1] < t) bad = true;
-        t = t < 0 ? 0 : (t > T ? T : t);
-        unit_off[i] = (a.unit == STRIDE_UNIT_TURN) ? t : a.L.turn_tok_off[t];
-        if (bad) raise_flag(a.flags, STRIDE_FLAG_BAD_OFFSETS);
-    }
-    if (i < R) a.stop_unit[i] = INT_MAX;
-    if (i < a.n_tiles) {
-        a.desc[i].status = 0;
-        a.desc[i].head = 0;
-        a.desc[i].value = 0.0;
-    }
-    if (i == 0) *a.counter = 0;
-}
-
 struct Seg {
     uint32_t f;
     double v;
@@ -113,185 +100,15 @@ __device__ __forceinline__ int64_t find_rollout(const int64_t *off, int64_t R, i
     return lo;
 }
 
-template <typename VT>
-__global__ __launch_bounds__(kScanThreads) void stop_scan_kernel(StopArgs a) {
-    __shared__ int64_t s_tile;
-    __shared__ Seg s_wave[kScanThreads / kWave];
-    __shared__ double s_carry;
-    __shared__ int32_t s_first[kSlots];
-    __shared__ int64_t s_r0;
-
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    if (tid == 0) s_tile = (int64_t)atomicAdd(a.counter, 1u);
-    for (int i = tid; i < kSlots; i += blockDim.x) s_first[i] = INT_MAX;
-    __syncthreads();
-    const int64_t tile = s_tile;
-    const int64_t u0 = tile * kScanTile;
-    const int64_t R = a.L.n_rollouts;
-    const VT *vals = static_cast<const VT *>(a.values);
-
-    // ---- load and thread-local segmented scan ----
-    const int64_t ubase = u0 + (int64_t)tid * kScanItems;
-    int64_t r = find_rollout(a.unit_off, R, ubase);
-    if (tid == 0) s_r0 = find_rollout(a.unit_off, R, u0);
-    double run[kScanItems];
-    uint8_t head[kScanItems];
-    int64_t rr[kScanItems];
-    Seg tagg{0u, 0.0};
-#pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        const int64_t u = ubase + j;
-        double v = 0.0;
-        uint8_t h = 0;
-        int64_t rj = -1;  // rollout holding unit u, -1 if none (only with bad offsets)
-        if (u < a.n_units && r >= 0) {
-            while (r + 1 < R && a.unit_off[r + 1] <= u) ++r;
-            const int64_t first = a.unit_off[r];
-            const int64_t n = a.unit_off[r + 1] - first;
-            const int64_t local = u - first;
-            if (local >= 0 && local < n) {
-                int64_t k0 = a.start ? (int64_t)a.start[r] : 0;
-                k0 = k0 < 0 ? 0 : (k0 > n ? n : k0);
-                h = (local == 0);
-                if (local >= k0) v = (double)vals[u];
-                rj = r;
-            }
-        }
-        rr[j] = rj;
-        head[j] = h;
-        tagg = combine(tagg, Seg{h, v});
-        run[j] = tagg.v;
-    }
-
-    // ---- block-level exclusive scan of the thread aggregates ----
-    Seg inc = tagg;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t f2 = __shfl_up(inc.f, off, kWave);
-        const double v2 = __shfl_up(inc.v, off, kWave);
-        if (lane >= off) inc = combine(Seg{f2, v2}, inc);
-    }
-    if (lane == kWave - 1) s_wave[wave] = inc;
-    __syncthreads();
-    Seg wpre{0u, 0.0};
-    for (int w = 0; w < wave; ++w) wpre = combine(wpre, s_wave[w]);
-    Seg excl;
-    {
-        const uint32_t f2 = __shfl_up(inc.f, 1, kWave);
-        const double v2 = __shfl_up(inc.v, 1, kWave);
-        excl = (lane == 0) ? wpre : combine(wpre, Seg{f2, v2});
-    }
-
-    // ---- publish the tile aggregate, then look back ----
-    if (tid == 0) {
-        Seg total{0u, 0.0};
-        for (int w = 0; w < kScanThreads / kWave; ++w) total = combine(total, s_wave[w]);
-#ifdef STRIDE_SCAN_DELAY_HOOK
-        if (a.delay_one_in) {
-            // splitmix64 step (Steele, Lea and Flood 2014) of (seed, tile): picks the tile
-            // and its sleep count
-            uint64_t z = a.delay_seed + 0x9E3779B97F4A7C15ull * (uint64_t)(tile + 1);
-            z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-            z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-            z ^= z >> 31;
-            if ((z % a.delay_one_in) == 0) {
-                const uint32_t n = 1 + (uint32_t)((z >> 32) % a.delay_sleeps);
-                for (uint32_t i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(127);
-            }
-        }
-#endif
-        a.desc[tile].value = total.v;
-        a.desc[tile].head = total.f;
-        __hip_atomic_store(&a.desc[tile].status, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-
-        double carry = 0.0;
-        const int64_t r0 = s_r0;
-        const bool continues = tile > 0 && r0 >= 0 && a.unit_off[r0] < u0;
-        if (continues) {
-#ifdef STRIDE_SCAN_DELAY_HOOK
-            const uint32_t limit = a.spin_limit ? a.spin_limit : kSpinLimit;
-#else
-            constexpr uint32_t limit = kSpinLimit;
-#endif
-            for (int64_t p = tile - 1; p >= 0; --p) {
-                uint32_t spins = 0;
-                while (__hip_atomic_load(&a.desc[p].status, __ATOMIC_ACQUIRE,
-                                         __HIP_MEMORY_SCOPE_AGENT) == 0u) {
-                    if (++spins > limit) break;
-                    __builtin_amdgcn_s_sleep(1);
-                }
-                if (spins > limit) {
-                    raise_flag(a.flags, STRIDE_FLAG_SPIN_LIMIT);
-                    carry = __builtin_nan("");
-                    break;
-                }
-                carry = a.desc[p].value + carry;
-                if (a.desc[p].head) break;
-            }
-        }
-        s_carry = carry;
-    }
-    __syncthreads();
-    const double carry = s_carry;
-    const int64_t r0 = s_r0;
-
-    // ---- cumulative values and first crossings ----
-    uint32_t seen = excl.f;
-    int64_t last_r = -2;
-#pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        const int64_t u = ubase + j;
-        if (u >= a.n_units) break;
-        const int64_t rj = rr[j];
-        seen |= head[j];
-        double c;
-        if (rj < 0) {
-            c = __builtin_nan("");
-        } else {
-            // thread-local running sum restarted at a head inside this thread's items
-            bool head_in_thread = false;
-            for (int q = 0; q <= j; ++q) head_in_thread |= (head[q] != 0);
-            c = head_in_thread ? run[j] : excl.v + run[j];
-            if (!seen) c += carry;
-        }
-        a.cum[u] = c;
-        if (rj < 0 || rj == last_r) continue;
-        const int64_t first = a.unit_off[rj];
-        const int64_t local = u - first;
-        int64_t k0 = a.start ? (int64_t)a.start[rj] : 0;
-        const int64_t n = a.unit_off[rj + 1] - first;
-        k0 = k0 < 0 ? 0 : (k0 > n ? n : k0);
-        const int32_t d = a.L.domain ? a.L.domain[rj] : 0;
-        const double lam = (d >= 0 && d < a.n_dom) ? a.lambda.v[d] : __builtin_nan("");
-        if (local >= k0 && c < lam) {
-            last_r = rj;  // later units of this rollout in this thread cannot be earlier
-            const int64_t slot = rj - r0;
-            if (r0 >= 0 && slot >= 0 && slot < kSlots)
-                atomicMin(&s_first[slot], (int32_t)local);
-            else
-                atomicMin(&a.stop_unit[rj], (int32_t)local);
-        }
-    }
-    __syncthreads();
-    if (r0 >= 0) {
-        for (int i = tid; i < kSlots; i += blockDim.x) {
-            if (s_first[i] != INT_MAX) atomicMin(&a.stop_unit[r0 + i], s_first[i]);
-        }
-    }
-}
-
-// stop_unit sentinel -> -1, retained row counts, bad domains.
-__global__ __launch_bounds__(256) void stop_finish_kernel(StopArgs a) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= a.L.n_rollouts) return;
+// What the stop test writes for a rollout: stop_unit (sentinel -> -1), retained rows, bad domains.
+// s: first crossing or INT_MAX; [first, first + n) its units.
+__device__ __forceinline__ void finish_rollout(const StopArgs &a, int64_t r, int32_t s,
+                                               int64_t first, int64_t n) {
     const int32_t d = a.L.domain ? a.L.domain[r] : 0;
     if (d < 0 || d >= a.n_dom) raise_flag(a.flags, STRIDE_FLAG_BAD_DOMAIN);
-    int32_t s = a.stop_unit[r];
     if (s == INT_MAX) s = -1;
     a.stop_unit[r] = s;
     if (!a.retained) return;
-    const int64_t first = a.unit_off[r];
-    int64_t n = a.unit_off[r + 1] - first;
     if (n < 0) n = 0;
     int64_t k0 = a.start ? (int64_t)a.start[r] : 0;
     k0 = k0 < 0 ? 0 : (k0 > n ? n : k0);
@@ -306,6 +123,440 @@ __global__ __launch_bounds__(256) void stop_finish_kernel(StopArgs a) {
         t1 = t1 > T ? T : t1;
         a.retained[r] = a.L.turn_tok_off[t1] - a.L.turn_tok_off[t0];
     }
+}
+
+// First unit of rollout i (i = R: the end of the last), from the layout; raises BAD_OFFSETS.
+__device__ __forceinline__ int64_t first_unit(const StopArgs &a, int64_t i) {
+    const int64_t R = a.L.n_rollouts, T = a.L.n_turns;
+    int64_t t = a.L.rollout_turn_off[i];
+    bool bad = t < 0 || t > T;
+    if (i == 0 && t != 0) bad = true;
+    if (i == R && t != T) bad = true;
+    if (i < R && a.L.rollout_turn_off[i + 1] < t) bad = true;
+    t = t < 0 ? 0 : (t > T ? T : t);
+    if (bad) raise_flag(a.flags, STRIDE_FLAG_BAD_OFFSETS);
+    return (a.unit == STRIDE_UNIT_TURN) ? t : a.L.turn_tok_off[t];
+}
+
+// unit_off, stop_unit sentinels, descriptor reset, tile counter reset.
+__global__ __launch_bounds__(256) void stop_prep_kernel(StopArgs a, int64_t *unit_off) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i <= a.L.n_rollouts) unit_off[i] = first_unit(a, i);
+    if (i < a.L.n_rollouts) a.stop_unit[i] = INT_MAX;
+    if (i < a.n_tiles) a.desc[i] = TileDesc{0, 0};
+    if (i == 0) *a.counter = 0;
+}
+
+// Tile descriptor: the aggregate's 64 bits in two words, each with its own tag (bit 0:
+// published, bit 1: a rollout starts in the tile) in the low half.  Each word is valid by
+// itself, so relaxed stores and loads suffice: no fence orders them, and none empties a cache.
+__device__ __forceinline__ void publish(TileDesc *d, double value, uint32_t head) {
+    const uint64_t v = (uint64_t)__double_as_longlong(value), tag = 1u | (head << 1);
+    __hip_atomic_store(&d->hi, (v & 0xFFFFFFFF00000000ull) | tag, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&d->lo, (v << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The carry into tile `tile` (called by its first wave): the aggregates of its predecessors,
+// added nearest first down to the first one that holds a rollout's start.  The lanes read 64
+// descriptors at once -- one round trip to memory where a walk takes one per tile -- and wait
+// only for those up to the nearest start; the additions keep the walk's order.
+__device__ __forceinline__ double look_back(const StopArgs &a, int64_t tile, int lane) {
+#ifdef STRIDE_SCAN_DELAY_HOOK
+    const uint32_t limit = a.spin_limit ? a.spin_limit : kSpinLimit;
+#else
+    constexpr uint32_t limit = kSpinLimit;
+#endif
+    double carry = 0.0;
+    for (int64_t base = tile - 1; base >= 0; base -= kWave) {
+        const int64_t p = base - lane;
+        bool ready = p < 0;  // lanes past tile 0 hold nothing
+        uint64_t hi = 0, lo = 0;
+        uint32_t spins = 0;
+        int need;
+        bool found;
+        for (;;) {
+            if (!ready) {
+                hi = __hip_atomic_load(&a.desc[p].hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                lo = __hip_atomic_load(&a.desc[p].lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ready = (hi & 1) && (lo & 1);
+            }
+            const uint64_t done = __ballot(ready);
+            const uint64_t heads = __ballot(ready && (hi & 2));
+            found = heads != 0;
+            need = found ? __builtin_ctzll(heads) + 1 : kWave;
+            const uint64_t upto = need == kWave ? ~0ull : (1ull << need) - 1;
+            if ((done & upto) == upto) break;
+            if (++spins > limit) {
+                if (lane == 0) raise_flag(a.flags, STRIDE_FLAG_SPIN_LIMIT);
+                return __builtin_nan("");
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        const uint64_t v = (hi & 0xFFFFFFFF00000000ull) | (lo >> 32);
+        const int n = base + 1 < need ? (int)(base + 1) : need;
+        for (int i = 0; i < n; ++i) {
+            const uint32_t vh = __builtin_amdgcn_readlane((uint32_t)(v >> 32), i);
+            const uint32_t vl = __builtin_amdgcn_readlane((uint32_t)v, i);
+            carry = __longlong_as_double((long long)(((uint64_t)vh << 32) | vl)) + carry;
+        }
+        if (found) break;
+    }
+    return carry;
+}
+
+// One workgroup per tile of kScanTile units, between stop_prep_kernel and stop_finish_kernel.
+// Latency bounds it (a tile reads 8 or 16 KB): the offsets, K0 and thresholds of the tile's
+// rollouts are fetched once into LDS (the first kSlots of them; rollouts past those come from
+// memory), so the searches and the per-unit tests make no dependent global loads.
+template <typename VT>
+__global__ __launch_bounds__(kScanThreads) void stop_scan_kernel(StopArgs a) {
+    constexpr int kCap = kSlots;
+    __shared__ int64_t s_tile;
+    __shared__ Seg s_wave[kScanThreads / kWave];
+    __shared__ double s_carry;
+    __shared__ int32_t s_first[kCap];
+    __shared__ int64_t s_off[kCap + 1];
+    __shared__ int64_t s_k0[kCap];
+    __shared__ double s_lam[kCap];
+    __shared__ int64_t s_r0;
+
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int64_t R = a.L.n_rollouts;
+    const VT *vals = static_cast<const VT *>(a.values);
+    if (tid == 0) s_tile = (int64_t)atomicAdd(a.counter, 1u);
+    __syncthreads();
+    const int64_t tile = s_tile;
+    const int64_t u0 = tile * kScanTile;
+    const int64_t ubase = u0 + (int64_t)tid * kScanItems;
+    VT in[kScanItems];
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) in[j] = ubase + j < a.n_units ? vals[ubase + j] : (VT)0;
+
+    // ---- the tile's rollouts ----
+    if (wave == 0) {  // last rollout with unit_off <= u0, 64 pivots at a time; -1 if none
+        int64_t lo = -1;
+        if (R > 0 && a.unit_off[0] <= u0) {
+            lo = 0;
+            for (int64_t hi = R; hi - lo > 1;) {
+                const int64_t step = (hi - lo + kWave - 1) / kWave, i = lo + lane * step;
+                const uint64_t le = __ballot(i < hi && a.unit_off[i] <= u0);
+                lo += (63 - __builtin_clzll(le)) * step;  // lane 0's pivot is always <= u0
+                hi = lo + step < hi ? lo + step : hi;
+            }
+        }
+        if (lane == 0) s_r0 = lo;
+    }
+    __syncthreads();
+    const int64_t r0 = s_r0, rb = r0 < 0 ? 0 : r0;  // rb: rollout of LDS entry 0
+    for (int i = tid; i <= kCap; i += kScanThreads) s_off[i] = a.unit_off[rb + i < R ? rb + i : R];
+    auto off = [&](int64_t r) -> int64_t {
+        return r - rb <= kCap ? s_off[r - rb] : a.unit_off[r];
+    };
+    auto prefix = [&](int64_t r, int64_t n) -> int64_t {  // K0 of rollout r, clamped
+        const int64_t k0 = a.start ? (int64_t)a.start[r] : 0;
+        return k0 < 0 ? 0 : (k0 > n ? n : k0);
+    };
+    auto limit = [&](int64_t r) -> double {
+        const int32_t d = a.L.domain ? a.L.domain[r] : 0;
+        return (d >= 0 && d < a.n_dom) ? a.lambda.v[d] : __builtin_nan("");
+    };
+    __syncthreads();
+    const int cnt = R - rb < kCap ? (int)(R - rb) : kCap;
+    for (int i = tid; i < cnt; i += kScanThreads) {
+        s_first[i] = INT_MAX;
+        s_k0[i] = prefix(rb + i, s_off[i + 1] - s_off[i]);
+        s_lam[i] = limit(rb + i);
+    }
+    __syncthreads();
+    // last rollout that starts at or before this thread's first unit, -1 if none
+    int64_t r = -1;
+    if (cnt > 0 && s_off[0] <= ubase) {
+        int lo = 0, hi = cnt;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (s_off[mid] <= ubase) lo = mid; else hi = mid;
+        }
+        r = rb + lo;
+        if (lo == kCap - 1 && r + 1 < R) r += find_rollout(a.unit_off + r, R - r, ubase);
+    }
+
+    // ---- thread-local segmented scan ----
+    double run[kScanItems];
+    bool head[kScanItems];
+    int64_t rr[kScanItems];
+    Seg tagg{0u, 0.0};
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+        const int64_t u = ubase + j;
+        double v = 0.0;
+        bool h = false;
+        int64_t rj = -1;  // rollout holding unit u, -1 if none (only with bad offsets)
+        if (u < a.n_units && r >= 0) {
+            while (r + 1 < R && off(r + 1) <= u) ++r;
+            const int64_t first = off(r), n = off(r + 1) - first, local = u - first;
+            if (local >= 0 && local < n) {
+                const int64_t k0 = r - rb < kCap ? s_k0[r - rb] : prefix(r, n);
+                h = (local == 0);
+                if (local >= k0) v = (double)in[j];
+                rj = r;
+            }
+        }
+        rr[j] = rj;
+        head[j] = h;
+        tagg = combine(tagg, Seg{h, v});
+        run[j] = tagg.v;
+    }
+
+    // ---- block-level exclusive scan of the thread aggregates ----
+    Seg inc = tagg;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t f2 = __shfl_up(inc.f, o, kWave);
+        const double v2 = __shfl_up(inc.v, o, kWave);
+        if (lane >= o) inc = combine(Seg{f2, v2}, inc);
+    }
+    if (lane == kWave - 1) s_wave[wave] = inc;
+    __syncthreads();
+    Seg wpre{0u, 0.0};
+    for (int w = 0; w < wave; ++w) wpre = combine(wpre, s_wave[w]);
+    Seg excl;
+    {
+        const uint32_t f2 = __shfl_up(inc.f, 1, kWave);
+        const double v2 = __shfl_up(inc.v, 1, kWave);
+        excl = (lane == 0) ? wpre : combine(wpre, Seg{f2, v2});
+    }
+
+    // ---- publish the tile aggregate, then look back ----
+    if (wave == 0) {
+        if (lane == 0) {
+            Seg total{0u, 0.0};
+            for (int w = 0; w < kScanThreads / kWave; ++w) total = combine(total, s_wave[w]);
+#ifdef STRIDE_SCAN_DELAY_HOOK
+            if (a.delay_one_in) {
+                // splitmix64 step (Steele, Lea and Flood 2014) of (seed, tile): picks the
+                // tile and its sleep count
+                uint64_t z = a.delay_seed + 0x9E3779B97F4A7C15ull * (uint64_t)(tile + 1);
+                z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+                z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+                z ^= z >> 31;
+                if ((z % a.delay_one_in) == 0) {
+                    const uint32_t n = 1 + (uint32_t)((z >> 32) % a.delay_sleeps);
+                    for (uint32_t i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(127);
+                }
+            }
+#endif
+            publish(&a.desc[tile], total.v, total.f);
+        }
+        double c = 0.0;
+        if (tile > 0 && r0 >= 0 && s_off[0] < u0) c = look_back(a, tile, lane);
+        if (lane == 0) s_carry = c;
+    }
+    __syncthreads();
+    const double carry = s_carry;
+
+    // ---- cumulative values and first crossings ----
+    bool seen = excl.f != 0, head_in_thread = false;
+    int64_t last_r = -2;
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+        const int64_t u = ubase + j;
+        if (u >= a.n_units) break;
+        const int64_t rj = rr[j];
+        seen |= head[j];
+        head_in_thread |= head[j];
+        double c;
+        if (rj < 0) {
+            c = __builtin_nan("");
+        } else {
+            // thread-local running sum restarted at a head inside this thread's items
+            c = head_in_thread ? run[j] : excl.v + run[j];
+            if (!seen) c += carry;
+        }
+        a.cum[u] = c;
+        if (rj < 0 || rj == last_r) continue;
+        const int64_t i = rj - rb, first = off(rj), local = u - first;
+        const bool in_lds = i < kCap;
+        const int64_t k0 = in_lds ? s_k0[i] : prefix(rj, off(rj + 1) - first);
+        if (local >= k0 && c < (in_lds ? s_lam[i] : limit(rj))) {
+            last_r = rj;  // later units of this rollout in this thread cannot be earlier
+            if (in_lds)
+                atomicMin(&s_first[i], (int32_t)local);
+            else
+                atomicMin(&a.stop_unit[rj], (int32_t)local);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < cnt; i += kScanThreads)
+        if (s_first[i] != INT_MAX) atomicMin(&a.stop_unit[rb + i], s_first[i]);
+}
+
+__global__ __launch_bounds__(256) void stop_finish_kernel(StopArgs a) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= a.L.n_rollouts) return;
+    finish_rollout(a, r, a.stop_unit[r], a.unit_off[r], a.unit_off[r + 1] - a.unit_off[r]);
+}
+
+// x + the lane's source under a data-parallel-primitive move (0 where the move has no source).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ double moved(double x) {
+    const uint64_t v = (uint64_t)__double_as_longlong(x);
+    const uint32_t l = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, kRows, 0xF, false);
+    const uint32_t h = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), kCtrl, kRows, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)h << 32) | l));
+}
+
+// Inclusive sum over the wave: within rows of 16 lanes (row_shr 1, 2, 4, 8), then row ends into
+// the next row (row_bcast 15) and the lower half's end into the upper half (row_bcast 31).
+// These moves are vector instructions, where __shfl_up goes through the LDS unit.  With loads and
+// stores of one unit each, it took 8.1 us for a chunk of 8,192 units; both changed, 3.0.
+__device__ __forceinline__ double wave_scan(double x) {
+    x += moved<0x111, 0xF>(x);
+    x += moved<0x112, 0xF>(x);
+    x += moved<0x114, 0xF>(x);
+    x += moved<0x118, 0xF>(x);
+    x += moved<0x142, 0xA>(x);
+    x += moved<0x143, 0xC>(x);
+    return x;
+}
+
+// Up to N consecutive elements from p on (p + j < end), as few loads as their number allows; the
+// addresses have the element's own alignment only, which global loads of several words accept.
+template <typename VT, int N>
+__device__ __forceinline__ void load_items(const VT *vals, int64_t u, int64_t hi, VT *x) {
+    constexpr int kPer = 16 / sizeof(VT) < N ? 16 / sizeof(VT) : N;
+    typedef VT Vec __attribute__((ext_vector_type(kPer), aligned(sizeof(VT))));
+    if (u + N <= hi) {
+#pragma unroll
+        for (int j = 0; j < N; j += kPer) {
+            const Vec v = *reinterpret_cast<const Vec *>(vals + u + j);
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) x[j + i] = v[i];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = u + j < hi ? vals[u + j] : (VT)0;
+    }
+}
+
+// The whole test of one rollout by a group of NT threads, NI units each at a time: no tiles, no
+// look-back, one launch.  The units run through a fixed scan (a thread's items in order, a
+// shuffle tree, waves in order, chunks in order), so cum is bit-reproducible; the next chunk's
+// values are in flight while one is scanned.  Latency bounds it: offsets, then values, K0 and
+// domain together, then a chunk after the other.  kRolloutUnits has what it measured.
+// Groups of one wave share a workgroup of 256 threads and meet no barrier.
+template <typename VT, int NT, int NI>
+__global__ __launch_bounds__(NT < 256 ? 256 : NT) void stop_rollout_kernel(StopArgs a) {
+    static_assert(NT == kWave || NT >= 256, "a group is one wave or a whole workgroup");
+    constexpr int kGroups = NT == kWave ? 4 : 1, kWaves = NT / kWave;
+    __shared__ double s_sum[2][kWaves];
+    __shared__ int32_t s_best[kWaves];
+    const int tid = threadIdx.x % NT, lane = threadIdx.x & (kWave - 1), wave = tid / kWave;
+    const int64_t R = a.L.n_rollouts, T = a.L.n_turns, U = a.n_units;
+    const int64_t r = (int64_t)blockIdx.x * kGroups + __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
+    if (r >= R) return;
+    const VT *vals = static_cast<const VT *>(a.values);
+    const int64_t t0 = a.L.rollout_turn_off[r], t1 = a.L.rollout_turn_off[r + 1];
+    const int32_t start = a.start ? a.start[r] : 0, d = a.L.domain ? a.L.domain[r] : 0;
+    if (tid == 0 && (t0 < 0 || t0 > T || (r == 0 && t0 != 0) || t1 < t0 ||
+                     (r == R - 1 && t1 != T)))
+        raise_flag(a.flags, STRIDE_FLAG_BAD_OFFSETS);
+    int64_t first = t0 < 0 ? 0 : (t0 > T ? T : t0), last = t1 < 0 ? 0 : (t1 > T ? T : t1);
+    if (a.unit == STRIDE_UNIT_TOKEN) {
+        first = a.L.turn_tok_off[first];
+        last = a.L.turn_tok_off[last];
+    }
+    const int64_t n = last - first;
+    int64_t k0 = start;
+    k0 = k0 < 0 ? 0 : (k0 > n ? n : k0);
+    const double lam = (d >= 0 && d < a.n_dom) ? a.lambda.v[d] : __builtin_nan("");
+    // offsets that do not cover [0, U) or leave it (flagged where they are not the caller's own
+    // row offsets): units in no rollout are NaN, and no access leaves [0, U)
+    const int64_t lo = first < 0 ? 0 : first, hi = last > U ? U : last;
+    if (r == 0)
+        for (int64_t u = tid; u < first && u < U; u += NT) a.cum[u] = __builtin_nan("");
+    if (r == R - 1)
+        for (int64_t u = (last < 0 ? 0 : last) + tid; u < U; u += NT) a.cum[u] = __builtin_nan("");
+    const int64_t from = first + k0 < lo ? lo : first + k0;
+    for (int64_t u = lo + tid; u < from && u < hi; u += NT) a.cum[u] = 0.0;
+
+    constexpr int64_t kChunk = (int64_t)NT * NI;
+    double carry = 0.0;
+    int32_t best = INT_MAX;
+    VT in[NI];
+    const int64_t mine = (int64_t)tid * NI;
+    load_items<VT, NI>(vals, from + mine, hi, in);
+    int buf = 0;
+    for (int64_t base = from; base < hi; base += kChunk, buf ^= 1) {
+        const int64_t u0 = base + mine;
+        VT next[NI];
+        load_items<VT, NI>(vals, u0 + kChunk, hi, next);
+        double run[NI];
+        run[0] = (double)in[0];
+#pragma unroll
+        for (int j = 1; j < NI; ++j) run[j] = run[j - 1] + (double)in[j];
+        const double inc = wave_scan(run[NI - 1]);
+        double pre = moved<0x138, 0xF>(inc), total;  // wave_shr 1: the lanes before this one
+        if (kWaves == 1) {
+            total = __shfl(inc, kWave - 1, kWave);
+        } else {
+            if (lane == kWave - 1) s_sum[buf][wave] = inc;
+            __syncthreads();  // the other buffer's readers are done before it is written again
+            double before = 0.0;
+            total = 0.0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const double v = s_sum[buf][w];
+                if (w == wave) before = total;
+                total += v;
+            }
+            pre += before;
+        }
+        pre += carry;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            run[j] += pre;
+            if (best == INT_MAX && u0 + j < hi && run[j] < lam) best = (int32_t)(u0 + j - first);
+        }
+        if (u0 + NI <= hi) {
+            typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
+#pragma unroll
+            for (int j = 0; j < NI; j += 2)
+                *reinterpret_cast<Pair *>(a.cum + u0 + j) = Pair{run[j], run[j + 1]};
+        } else {
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                if (u0 + j < hi) a.cum[u0 + j] = run[j];
+        }
+        carry += total;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) in[j] = next[j];
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const int32_t b = __shfl_xor(best, o, kWave);
+        best = b < best ? b : best;
+    }
+    if (kWaves > 1) {
+        if (lane == 0) s_best[wave] = best;
+        __syncthreads();
+        if (tid == 0)
+            for (int w = 1; w < kWaves; ++w) best = s_best[w] < best ? s_best[w] : best;
+    }
+    if (tid == 0) finish_rollout(a, r, best, first, n);
+}
+
+template <typename VT>
+static hipError_t launch_stop_rollouts(const StopArgs &a, int64_t per, hipStream_t stream) {
+    const unsigned R = (unsigned)a.L.n_rollouts;
+    // Threads by the rollouts' average length: enough for one chunk or two of it.
+    if (per <= 128)
+        hipLaunchKernelGGL((stop_rollout_kernel<VT, 64, 2>), dim3((R + 3) / 4), dim3(256), 0, stream, a);
+    else if (per <= 1024)
+        hipLaunchKernelGGL((stop_rollout_kernel<VT, 256, 4>), dim3(R), dim3(256), 0, stream, a);
+    else
+        hipLaunchKernelGGL((stop_rollout_kernel<VT, 1024, 8>), dim3(R), dim3(1024), 0, stream, a);
+    return hipGetLastError();
 }
 
 // Online form of the stop test (Algorithm 1's inner loop while a rollout is being
@@ -429,6 +680,12 @@ hipError_t launch_stop(const stride_layout &L, int32_t unit, const void *values,
     a.spin_limit = 0;
 #endif
 
+    const int64_t per = L.n_rollouts > 0 ? n_units / L.n_rollouts : 0;
+    if (L.n_rollouts > 0 && n_units <= kRolloutUnits && per <= kRolloutLength) {
+        if (unit == STRIDE_UNIT_TURN)
+            return launch_stop_rollouts<double>(a, per, stream);
+        return launch_stop_rollouts<float>(a, per, stream);
+    }
     const int64_t prep_n = (L.n_rollouts + 1 > a.n_tiles) ? L.n_rollouts + 1 : a.n_tiles;
     hipLaunchKernelGGL(stop_prep_kernel, dim3((unsigned)((prep_n + 255) / 256)), dim3(256), 0,
                        stream, a, reinterpret_cast<int64_t *>(base + w.unit_off));

@@ -1,0 +1,86 @@
+"""The stop test and restart pick with a group of threads per rollout (one wave, one workgroup of
+256, or one of 1,024 / 512 threads, by the average rollout), against the oracle: rollouts at the
+edges of a group's chunk, empty rollouts, a K0 at the end, both units, and offsets that do not
+cover the units."""
+import numpy as np
+import pytest
+
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+SIZES = {  # lengths at the edges of a chunk of 128, 1,024 and 8,192 (restart: 128, 2,048, 4,096) units
+    "wave": [1, 0, 127, 128, 129, 0, 2, 300, 63, 64, 65, 1, 255, 256, 257, 3, 0],
+    "block": [1023, 1024, 1025, 1, 0, 2047, 2048, 2049, 255, 257, 700, 5],
+    "wide": [8191, 8192, 8193, 1, 0, 4095, 4096, 4097, 16385, 12289, 2],
+    "skewed": [40000] + [3] * 1500,
+    "tiles": [140000, 1, 0, 2048],   # past the average a group takes: the tile scan
+}
+
+
+@pytest.mark.parametrize("unit", ["turn", "token"])
+@pytest.mark.parametrize("name", list(SIZES))
+def test_groups_against_the_oracle(name, unit):
+    import torch
+    import paper_2609_14636_amd as P
+    g = np.random.default_rng(len(name) + (unit == "turn"))
+    sizes = np.array(SIZES[name])
+    R = sizes.size
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    U = int(off[-1])
+    if unit == "token":
+        rto, tto = np.arange(R + 1, dtype=np.int32), off
+    else:
+        rto, tto = off.astype(np.int32), np.concatenate([[0], np.cumsum(g.integers(0, 4, U))]).astype(np.int64)
+    N = int(tto[-1])
+    vals = -np.abs(g.normal(0.5, 0.5, size=U))
+    vals[g.random(U) < 0.002] = -np.inf if unit == "token" else -30.0
+    vals = vals.astype(np.float32 if unit == "token" else np.float64)
+    lam, alpha = [-0.3 * sizes.max(), -40.0, -np.inf], [-1.9, -np.inf, -4.0]
+    dom = g.integers(0, 3, size=R).astype(np.int32)
+    start = (g.random(R) * sizes * 0.4).astype(np.int32)
+    start[::5] = sizes[::5] + 7   # past the end: clamped to the rollout's length
+    start[1::7] = -3
+    mask = (g.random(U) < 0.999).astype(np.uint8)
+    k0 = np.clip(start, 0, sizes).astype(np.int32)
+    rows = tto if unit == "turn" else np.arange(U + 1, dtype=np.int64)
+    cum_o, stop_o, ret_o = H.OP.O.stop(off, vals.astype(np.float64), np.array(lam)[dom], k0, rows)
+    rec = np.where(stop_o >= 0, stop_o + 1, sizes).astype(np.int32)
+    ks_o, k0_o, km_o = H.OP.O.restart(off, vals.astype(np.float64), rec, np.array(alpha)[dom], mask)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    lay = P.Layout(dev(rto), dev(tto), N, dev(dom))
+    code = P.STRIDE_UNIT_TOKEN if unit == "token" else P.STRIDE_UNIT_TURN
+    path = P.Path(lay, code, with_student=False)
+    for t in (path.cum, path.stop_unit, path.retained, path.k_star, path.k0, path.k_max):
+        t.fill_(77)
+    P.stride_stop(lay, code, dev(vals), lam, dev(start), path.cum, path.stop_unit, path.retained,
+                  path.flags, path.ws)
+    P.stride_restart_turn(lay, code, dev(vals), path.stop_unit, alpha, dev(mask), path.k_star,
+                          path.k0, path.k_max, path.flags)
+    got = path.host()
+    assert got["flags"] == 0
+    fin = np.isfinite(cum_o)
+    assert np.array_equal(got["cum"][~fin], cum_o[~fin])
+    # sums of at most 16,385 doubles in another order: far below 1e-9 of their size
+    assert np.all(np.abs(got["cum"][fin] - cum_o[fin]) <= 1e-9 * np.maximum(np.abs(cum_o[fin]), 1))
+    for k, o in (("stop_unit", stop_o), ("retained", ret_o), ("k_star", ks_o), ("k0", k0_o), ("k_max", km_o)):
+        assert np.array_equal(got[k], o), k
+
+
+def test_units_in_no_rollout():
+    """Offsets that start late or end early are flagged; the units in no rollout are NaN and
+    nothing past the arrays is written."""
+    import torch
+    import paper_2609_14636_amd as P
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    lay = P.Layout(dev(np.array([3, 5, 9], np.int32)), dev(np.arange(13, dtype=np.int64)), 12)
+    cum = torch.full((20,), 5.0, dtype=torch.float64, device="cuda")
+    stop = torch.full((2,), 5, dtype=torch.int32, device="cuda")
+    flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(P.stride_workspace_size(lay, P.STRIDE_UNIT_TURN), dtype=torch.uint8, device="cuda")
+    vals = -torch.ones(12, dtype=torch.float64, device="cuda")
+    P.stride_stop(lay, P.STRIDE_UNIT_TURN, vals, [-2.5], None, cum, stop, None, flags, ws)
+    assert int(flags.item()) == P.STRIDE_FLAG_BAD_OFFSETS
+    c = cum.cpu().numpy()
+    assert np.isnan(c[:3]).all() and np.isnan(c[9:12]).all() and (c[12:] == 5.0).all()
+    assert c[3:9].tolist() == [-1, -2, -1, -2, -3, -4] and stop.tolist() == [-1, 2]
