@@ -3,9 +3,8 @@
 // Eq. (1) (Sec. 3.1): log pi(y_t | y_<t) = x[y_t] - log sum_v exp(x[v]) over the
 // row's V logits.  Each row is read exactly once from HBM.
 //
-// Design (gfx950, wave64): one wavefront per row; a workgroup holds eight
-// independent rows (small batches instead share each row among the eight
-// wavefronts of a workgroup: score_rows_split_kernel).  Lanes stream the row
+// Design (gfx950, wave64): one wavefront, or 4, 8 or 16 wavefronts of a workgroup,
+// per row (score_rows_kernel).  Lanes stream the row
 // with 16-byte non-temporal loads (8 bf16 or 4 fp32 per load, consecutive
 // lanes on consecutive 16-byte words, so one wave instruction moves 1 KiB,
 // fully coalesced).  Each lane keeps a
@@ -23,12 +22,7 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.69314718055994531f;
 constexpr uint8_t kBadDomain = 0xFF;
-// Row items (teacher and student rows) below which each row gets a workgroup of kSplitWaves
-// wavefronts instead of one wavefront.  Measured on V = 151,936 bf16 rows: the shared rows read
-// as fast or faster up to 16,384 items (64 rows: 14 us against 61 us) and 1-2% slower from
-// 32,768 items on, where one wavefront per row already fills the chip.
-constexpr int kSplitWaves = 8;
-constexpr int64_t kSplitBelow = 16384;
+constexpr int kSplitWaves = 8;  // wavefronts that share a token's two rows in the paired pass
 // Tokens below which the paired pass (exact KL) shares each token's two rows the same way:
 // measured, the shared form is as fast or faster up to 65,536 tokens (64 tokens: 25 us against
 // 108 us) and 0.7-1.4% slower at 85,185 and 131,072.
@@ -40,11 +34,13 @@ template <int DT>
 struct Elem;
 template <>
 struct Elem<STRIDE_BF16> {
+    static constexpr uint32_t kNegInf = 0xFF80FF80u;
     static constexpr int kPerVec = 8;
     static constexpr int kSize = 2;
 };
 template <>
 struct Elem<STRIDE_F32> {
+    static constexpr uint32_t kNegInf = 0xFF800000u;
     static constexpr int kPerVec = 4;
     static constexpr int kSize = 4;
 };
@@ -124,12 +120,17 @@ __device__ __forceinline__ void wave_merge(float &m, float &s) {
     }
 }
 
-// The row's result from its (max, sum): log pi(y) = x_y - m - log s, NaN and a flag for a
-// non-finite row or a token id outside [0, V).
 template <int DT>
-__device__ __forceinline__ void write_row(const ScoreArgs &a, int64_t row, const u32x4 *p, float m,
-                                          float s, float *out) {
-    const int32_t y = a.ids[row];
+__device__ __forceinline__ float element(const u32x4 *p, int32_t i) {
+    if (DT == STRIDE_BF16)
+        return __uint_as_float((uint32_t)(reinterpret_cast<const uint16_t *>(p)[i]) << 16);
+    return reinterpret_cast<const float *>(p)[i];
+}
+
+// The row's result from its (max, sum) and sampled logit: log pi(y) = x_y - m - log s, NaN and a
+// flag for a non-finite row or a token id outside [0, V).
+__device__ __forceinline__ void write_row(const ScoreArgs &a, int64_t row, int32_t y, float xy,
+                                          float m, float s, float *out) {
     float r;
     uint32_t bad = 0;
     const bool finite = (m > -INFINITY) && (m < INFINITY) && (s > 0.0f) && (s < INFINITY);
@@ -139,11 +140,6 @@ __device__ __forceinline__ void write_row(const ScoreArgs &a, int64_t row, const
         r = __builtin_nanf("");
         raise_flag(a.flags, bad);
     } else {
-        float xy;
-        if (DT == STRIDE_BF16)
-            xy = __uint_as_float((uint32_t)(reinterpret_cast<const uint16_t *>(p)[y]) << 16);
-        else
-            xy = reinterpret_cast<const float *>(p)[y];
         // At most 0: the maximum's own term is 1 in exact arithmetic.  Here it is exp2 of the
         // rounding residual of m * log2(e) (the exponent argument is one fma against that
         // rounded product), which can sit a few 1e-7 below 1; the clamp removes only that
@@ -153,14 +149,24 @@ __device__ __forceinline__ void write_row(const ScoreArgs &a, int64_t row, const
     out[row] = r;
 }
 
-template <int DT, int U>
-__global__ __launch_bounds__(kRowThreads) void score_rows_kernel(ScoreArgs a) {
+// W wavefronts share a row, RW rows per workgroup, D chunks of U loads per wavefront: wavefront w
+// folds the row's chunks w, w + W, ... with the next D - 1 in flight, and its share of the words
+// after the last whole chunk, which it fetches first.  The wavefronts' (max, sum) states are
+// merged in their order through LDS, so the result does not depend on timing (the forms differ
+// in the order of rounding only).  HBM bounds it while there are rows for every CU.
+// launch_score_rows has the choice of a form and what it measured.
+template <int DT, int W, int RW, int U, int D>
+__global__ __launch_bounds__(W *RW *kWave) void score_rows_kernel(ScoreArgs a) {
+    static_assert(W == 1 || RW == 1, "wavefronts that share a row meet at a workgroup barrier");
     constexpr int E = Elem<DT>::kPerVec;
+    __shared__ float s_m[W], s_s[W], s_xy;
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t item = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wave = W == 1 ? 0 : wid;
+    const int64_t item = (int64_t)blockIdx.x * RW + (W == 1 ? wid : 0);
     const bool two = a.student != nullptr;
     const int64_t n_items = two ? 2 * a.n_rows : a.n_rows;
-    if (item >= n_items) return;
+    if (item >= n_items) return;  // W > 1: never, the grid has exactly n_items workgroups
     const bool is_student = two && (item & 1);
     const int64_t row = two ? (item >> 1) : item;
     float *out = is_student ? a.logp_s : a.logp_t;
@@ -170,127 +176,104 @@ __global__ __launch_bounds__(kRowThreads) void score_rows_kernel(ScoreArgs a) {
         base = a.student;
     } else {
         const int d = a.row_dom ? (int)a.row_dom[row] : 0;
-        if (d >= a.n_teachers) {  // row not covered by the layout or bad domain (already flagged)
-            if (lane == 0) out[row] = __builtin_nanf("");
+        // row not covered by the layout or bad domain (already flagged); the same for all
+        // wavefronts of the row, which leave before any barrier
+        if (d >= a.n_teachers) {
+            if (wave == 0 && lane == 0) out[row] = __builtin_nanf("");
             return;
         }
         base = a.teachers.p[d];
     }
     const u32x4 *p = reinterpret_cast<const u32x4 *>(static_cast<const char *>(base) +
                                                      row * a.ld * Elem<DT>::kSize);
-    const int64_t nvec = a.vocab / E;  // 16-byte words lying wholly inside [0, vocab)
+    const int32_t y = a.ids[row];
+    const int nvec = a.vocab / E;  // 16-byte words lying wholly inside [0, vocab)
     const int tail = a.vocab % E;
+    constexpr int kStep = U * kWave;
+    const int nfull = nvec / kStep;  // whole chunks
+    const int mine = nfull > wave ? (nfull - wave + W - 1) / W : 0;
 
     float m = -INFINITY, s0 = 0.0f, s1 = 0.0f;
-    int64_t k = 0;
-    constexpr int64_t kStep = (int64_t)U * kWave;
-    for (; k + kStep <= nvec; k += kStep) {
-        u32x4 v[U];
+    auto load = [&](int i, u32x4 *v) __attribute__((always_inline)) {
+        const u32x4 *q = p + (int64_t)(wave + i * W) * kStep + lane;
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(p + k + u * kWave + lane);
+        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(q + u * kWave);
+    };
+    auto use = [&](const u32x4 *v) __attribute__((always_inline)) {
         float x[U * E];
 #pragma unroll
         for (int u = 0; u < U; ++u) unpack<DT>(v[u], x + u * E);
         fold<U * E>(m, s0, s1, x);
+    };
+    // words after the last whole chunk, every W-th block of 64 of them; -inf past the row
+    constexpr int kRest = (U + W - 1) / W;
+    u32x4 rest[kRest];
+#pragma unroll
+    for (int i = 0; i < kRest; ++i) {
+        const int k = nfull * kStep + (i * W + wave) * kWave + lane;
+        constexpr uint32_t n = Elem<DT>::kNegInf;
+        rest[i] = u32x4{n, n, n, n};
+        if (k < nvec) rest[i] = __builtin_nontemporal_load(p + k);
     }
-    for (; k < nvec; k += kWave) {
-        if (k + lane < nvec) {
-            u32x4 v = __builtin_nontemporal_load(p + k + lane);
-            float x[E];
-            unpack<DT>(v, x);
-            fold<E>(m, s0, s1, x);
+    u32x4 v[D][U];
+    if (D == 1) {
+        for (int i = 0; i < mine; ++i) {
+            load(i, v[0]);
+            use(v[0]);
+        }
+    } else {
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d)
+            if (d < mine) load(d, v[d]);
+        int i = 0;
+        for (; i + 2 * D - 2 < mine; i += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                load(i + d + D - 1, v[(d + D - 1) % D]);
+                use(v[d]);
+            }
+        }
+        // at most 2 D - 2 chunks left, the first D - 1 of them in flight
+#pragma unroll
+        for (int d = 0; d < 2 * D - 2; ++d) {
+            if (i + d + D - 1 < mine) load(i + d + D - 1, v[(d + D - 1) % D]);
+            if (i + d < mine) use(v[d % D]);
         }
     }
-    if (tail && lane == 0) {
-        // The last word also holds ld - vocab padding elements: mask them out.
-        u32x4 v = p[nvec];
+#pragma unroll
+    for (int i = 0; i < kRest; ++i) {
         float x[E];
-        unpack<DT>(v, x);
-#pragma unroll
-        for (int j = 0; j < E; ++j)
-            if (j >= tail) x[j] = -INFINITY;
+        unpack<DT>(rest[i], x);
         fold<E>(m, s0, s1, x);
-    }
-    float s = s0 + s1;
-    wave_merge(m, s);
-    if (lane == 0) write_row<DT>(a, row, p, m, s, out);
-}
-
-// Batches too small to fill the chip with one wavefront per row (the online setting scores a
-// few hundred rows per call): a workgroup of kSplitWaves wavefronts shares each row.  Wave w
-// folds the row's U-load chunks w, w + kSplitWaves, ... and every kSplitWaves-th of the words
-// after the last whole chunk; the waves' (max, sum) states are merged in wave order through
-// LDS, so the result does not depend on timing (it differs from score_rows_kernel's only in
-// the order of rounding).
-template <int DT, int U>
-__global__ __launch_bounds__(kSplitWaves *kWave) void score_rows_split_kernel(ScoreArgs a) {
-    constexpr int E = Elem<DT>::kPerVec;
-    __shared__ float s_m[kSplitWaves], s_s[kSplitWaves];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int64_t item = blockIdx.x;  // one workgroup per item: the grid has exactly n_items
-    const bool two = a.student != nullptr;
-    const bool is_student = two && (item & 1);
-    const int64_t row = two ? (item >> 1) : item;
-    float *out = is_student ? a.logp_s : a.logp_t;
-
-    const void *base;
-    if (is_student) {
-        base = a.student;
-    } else {
-        const int d = a.row_dom ? (int)a.row_dom[row] : 0;
-        if (d >= a.n_teachers) {  // the same for the whole workgroup: it leaves before any barrier
-            if (threadIdx.x == 0) out[row] = __builtin_nanf("");
-            return;
-        }
-        base = a.teachers.p[d];
-    }
-    const u32x4 *p = reinterpret_cast<const u32x4 *>(static_cast<const char *>(base) +
-                                                     row * a.ld * Elem<DT>::kSize);
-    const int64_t nvec = a.vocab / E;
-    const int tail = a.vocab % E;
-    constexpr int64_t kStep = (int64_t)U * kWave;
-    const int64_t nfull = nvec / kStep;  // whole U-load chunks
-
-    float m = -INFINITY, s0 = 0.0f, s1 = 0.0f;
-    for (int64_t c = wave; c < nfull; c += kSplitWaves) {
-        const int64_t k = c * kStep;
-        u32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(p + k + u * kWave + lane);
-        float x[U * E];
-#pragma unroll
-        for (int u = 0; u < U; ++u) unpack<DT>(v[u], x + u * E);
-        fold<U * E>(m, s0, s1, x);
-    }
-    for (int64_t k = nfull * kStep + (int64_t)wave * kWave; k < nvec; k += (int64_t)kSplitWaves * kWave) {
-        if (k + lane < nvec) {
-            u32x4 v = __builtin_nontemporal_load(p + k + lane);
-            float x[E];
-            unpack<DT>(v, x);
-            fold<E>(m, s0, s1, x);
-        }
     }
     if (tail && wave == 0 && lane == 0) {
-        u32x4 v = p[nvec];
+        // The last word also holds ld - vocab padding elements: mask them out.
         float x[E];
-        unpack<DT>(v, x);
+        unpack<DT>(p[nvec], x);
 #pragma unroll
         for (int j = 0; j < E; ++j)
             if (j >= tail) x[j] = -INFINITY;
         fold<E>(m, s0, s1, x);
     }
+    // The sampled logit is the last wavefront's: it has the fewest chunks, so the others' loads
+    // cover this one (before the row it would hold up the wavefront until the token id is there).
+    float xy = 0.0f;
+    if (wave == W - 1 && y >= 0 && y < a.vocab) xy = element<DT>(p, y);
     float s = s0 + s1;
     wave_merge(m, s);
-    if (lane == 0) {
-        s_m[wave] = m;
-        s_s[wave] = s;
+    if (W > 1) {
+        if (lane == 0) {
+            s_m[wave] = m;
+            s_s[wave] = s;
+            if (wave == W - 1) s_xy = xy;
+        }
+        __syncthreads();
+        if (wave != 0) return;
+        xy = s_xy;
+#pragma unroll
+        for (int w = 1; w < W; ++w) merge(m, s, s_m[w], s_s[w]);
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {  // wave 0's state, then waves 1, 2, ... in order
-        for (int w = 1; w < kSplitWaves; ++w) merge(m, s, s_m[w], s_s[w]);
-        write_row<DT>(a, row, p, m, s, out);
-    }
+    if (lane == 0) write_row(a, row, y, xy, m, s, out);
 }
 
 // Exact reverse KL in the same pass: one wavefront per token streams the teacher
@@ -595,6 +578,39 @@ __global__ __launch_bounds__(256) void row_domain_kernel(stride_layout L, int32_
     row_dom[i] = (uint8_t)d;
 }
 
+template <int DT, int W, int RW, int U, int D>
+hipError_t launch_rows_form(const ScoreArgs &a, hipStream_t stream) {
+    const int64_t items = a.student ? 2 * a.n_rows : a.n_rows;
+    hipLaunchKernelGGL((score_rows_kernel<DT, W, RW, U, D>), dim3((unsigned)((items + RW - 1) / RW)),
+                       dim3(W * RW * kWave), 0, stream, a);
+    return hipGetLastError();
+}
+
+// The form by the row's 16-byte words and the number of rows.  More wavefronts per row read fewer
+// rows at a time, and leave less of the chip idle at the end, but each needs words enough for its
+// loads.  Teacher and student rows, bf16, one wavefront per row -> the form taken here:
+//   words  125, 60,000 rows: 57.6 -> 36.1 us (U = 4 instead of 8; eight wavefronts 131)
+//   words 2,000, 60,000 rows: 282 -> 274 us; 2,000 rows 13.8 -> 12.5
+//   words 4,000, 60,000 rows: 561 -> 524 us; words 6,250, 32,768 rows: 480 -> 458
+//   words 12,500, 80,000 rows: 2,368 -> 2,252 us (U = 8, one chunk at a time: 2,260)
+//   words 18,992: 128 rows 58 -> 11 us, 8,192 rows 383 -> 362 (sixteen wavefronts 366),
+//                 32,768 rows 1,444 -> 1,425 (eight 1,435), 174,554 rows 7,681 -> 7,637 (7,669)
+// Sixteen wavefronts pay at two or three of their rounds of 8,192 words: 1,201 against 1,211 us
+// at 16,384 words, 1% slower than eight at 25,000.  fp32 rows hold half the arithmetic per word and
+// leave registers for two such workgroups per CU: sixteen from 8,192 words on (853 against 869 us
+// at 12,500 words, 30,000 rows).
+template <int DT>
+hipError_t launch_rows(const ScoreArgs &a, hipStream_t stream) {
+    const int words = a.vocab / Elem<DT>::kPerVec;
+    const bool many = (a.student ? 2 * a.n_rows : a.n_rows) >= 16384;
+    if (words < 1024) return launch_rows_form<DT, 1, 8, 4, 1>(a, stream);
+    if (words < 3072) return launch_rows_form<DT, 4, 1, 8, 1>(a, stream);
+    if (words < 8192) return launch_rows_form<DT, 8, 1, 8, 1>(a, stream);
+    if (many && (DT == STRIDE_F32 || (words >= 16384 && words < 24576)))
+        return launch_rows_form<DT, 16, 1, 8, 1>(a, stream);
+    return launch_rows_form<DT, 8, 1, 4, 3>(a, stream);
+}
+
 }  // namespace
 
 hipError_t launch_score_pairs(int32_t dtype, const PtrTable &teachers, int32_t n_teachers,
@@ -660,25 +676,8 @@ hipError_t launch_score_rows(int32_t dtype, const PtrTable &teachers, int32_t n_
     a.ld = ld;
     a.vocab = vocab;
     a.n_teachers = n_teachers;
-    const int64_t items = student ? 2 * n_rows : n_rows;
-    if (items < kSplitBelow) {
-        if (dtype == STRIDE_BF16)
-            hipLaunchKernelGGL((score_rows_split_kernel<STRIDE_BF16, 8>), dim3((unsigned)items),
-                               dim3(kSplitWaves * kWave), 0, stream, a);
-        else
-            hipLaunchKernelGGL((score_rows_split_kernel<STRIDE_F32, 8>), dim3((unsigned)items),
-                               dim3(kSplitWaves * kWave), 0, stream, a);
-        return hipGetLastError();
-    }
-    constexpr int kRowsPerBlock = kRowThreads / kWave;
-    const int64_t blocks = (items + kRowsPerBlock - 1) / kRowsPerBlock;
-    if (dtype == STRIDE_BF16)
-        hipLaunchKernelGGL((score_rows_kernel<STRIDE_BF16, 8>), dim3((unsigned)blocks), dim3(kRowThreads),
-                           0, stream, a);
-    else
-        hipLaunchKernelGGL((score_rows_kernel<STRIDE_F32, 8>), dim3((unsigned)blocks), dim3(kRowThreads),
-                           0, stream, a);
-    return hipGetLastError();
+    if (dtype == STRIDE_BF16) return launch_rows<STRIDE_BF16>(a, stream);
+    return launch_rows<STRIDE_F32>(a, stream);
 }
 
 }  // namespace stride

@@ -1,0 +1,67 @@
+"""Every form of the row-scoring kernel (1, 4, 8 or 16 wavefronts per row, by the row's 16-byte
+words and the number of rows) on both sides of its borders, against float64: ragged tails, rows
+whose last chunk is partial, -inf entries, a row of only -inf and one with a NaN."""
+import math
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# 16-byte words per row at and around the borders, and the chunk counts of the pipelined form
+FEW = [1, 63, 65, 255, 256, 257, 1023, 1024, 1025, 2047, 3071, 3072, 3073, 4095, 7937, 8191, 8192, 8193,
+       8447, 8448, 9500, 10243, 12365, 14336, 16383, 16384, 18992, 24576]
+MANY = [8192, 8703, 16384, 16999, 20480, 24575, 24576]
+
+
+def _check(words, n, dtype, pad):
+    import torch
+    import paper_2609_14636_amd as P
+    per = 8 if dtype is torch.bfloat16 else 4
+    vocab = words * per + pad
+    ld = vocab + (-vocab) % per
+    g = torch.Generator(device="cuda").manual_seed(words + n)
+    x = torch.empty((n, ld), dtype=dtype, device="cuda").normal_(0, 3, generator=g)
+    ids = torch.randint(0, vocab, (n,), dtype=torch.int32, device="cuda", generator=g)
+    ids[0], ids[1] = vocab - 1, 0
+    x[:, vocab:] = 1000.0                       # padding columns are not logits
+    if vocab > 4:
+        x[2, :vocab - 1] = -math.inf            # only the last entry has mass
+        ids[2] = vocab - 1
+        x[3, ::3] = -math.inf
+        ids[3] = 1
+    x[4, :vocab] = -math.inf
+    x[5, vocab // 2] = math.nan
+    ids[6], ids[7] = vocab, -1
+    lay = P.Layout(torch.tensor([0, 1], dtype=torch.int32, device="cuda"),
+                   torch.tensor([0, n], dtype=torch.int64, device="cuda"), n)
+    path = P.Path(lay, P.STRIDE_UNIT_TURN, with_student=False)
+    path.score(vocab, [x], None, ids)
+    got = path.logp_t
+    assert torch.isnan(got[4:8]).all()
+    assert int(path.flags.item()) & (P.STRIDE_FLAG_NONFINITE | P.STRIDE_FLAG_TOKEN_OOB) == \
+        P.STRIDE_FLAG_NONFINITE | P.STRIDE_FLAG_TOKEN_OOB
+    at = torch.tensor([0, 1, 2, 3] + list(range(8, n, max(1, n // 64))) + [n - 1], device="cuda")
+    z = x[at][:, :vocab].double()
+    want = z.gather(1, ids[at].long().unsqueeze(1)).squeeze(1) - torch.logsumexp(z, 1)
+    # fp32 sums of at most a few hundred terms per lane and their merges, and the rounding of
+    # a logarithm and two differences of numbers below 64: a few units of 2^-18
+    assert float((got[at].double() - want).abs().max()) <= 2e-5
+    # one term, exp2 of the rounding residual of m log2(e): within 5e-7 of its exact value 0
+    assert vocab <= 4 or -5e-7 <= float(got[2]) <= 0.0
+
+
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_few_rows(dtype, pad):
+    import torch
+    for words in FEW:
+        print("words", words, flush=True)
+        _check(words, 40, torch.bfloat16 if dtype == "bf16" else torch.float32, pad)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_many_rows(dtype):
+    import torch
+    for words in MANY:
+        print("words", words, flush=True)
+        _check(words, 16384 + 5, torch.bfloat16 if dtype == "bf16" else torch.float32, 1)
