@@ -17,9 +17,9 @@
 //   unit always has a wave with work.  K = d streams in 64-wide stages through a
 //   ring of five 32 KB LDS buffers (the whole 160 KB LDS), each holding one
 //   operand of one stage, filled by direct buffer->LDS loads (buffer_load_dwordx4
-//   ... lds, no register staging): H of stage j in buffer 2j mod 5, W in 2j+1 mod 5.
-//   Every memory phase issues one operand's loads -- W(j+1) in the first half of
-//   stage j, H(j+2) in the second -- so the loads are spread evenly over the
+//   ... lds, no register staging): W of stage j in buffer 2j mod 5, H in 2j+1 mod 5.
+//   Every memory phase issues one operand's loads -- H(j+1) in the first half of
+//   stage j, W(j+2) in the second -- so the loads are spread evenly over the
 //   phases and each has two to four phases to land.  Eight lanes load one row's
 //   128 bytes, a whole cache line, and rows are XOR-swizzled so the 16-byte
 //   fragment reads are free of bank conflicts.  No vector ALU work remains in the
@@ -40,6 +40,7 @@
 //   super-row.  Row tiles and vocabulary tiles past the last whole super-tile
 //   are numbered apart, without holes (tile_of), so that every XCD and every
 //   shader engine of it has the same share of them.
+//   Up to 128 rows a kernel of its own streams W through registers (fused_rows).
 // Kernel 2: z_y = h . w_y per row (one wave per row, fp32), the merge of each row's V/128
 //   partials, and log pi_T(y) = (z_y - m) - log s.
 #include <atomic>
@@ -164,7 +165,8 @@ __device__ __forceinline__ void tile_of(const FusedArgs &a, int b, int &tm, int 
     tn = (s / h) * 8 + xcd;
 }
 
-__global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
+template <bool kAlone>
+__device__ __forceinline__ void fused_lse(const FusedArgs &a) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     // wave-uniform values in scalar registers: the LDS-DMA destinations are scalar arithmetic
@@ -179,6 +181,12 @@ __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
     const int64_t m0 = (int64_t)tm * kBM;
     const int64_t n0 = (int64_t)tn * kBN;
     const int d = a.d, ns = d / kBK;
+    // kAlone (one row tile, so no other tile shares this one's W): a tile starts at a K stage of its
+    // own.  With all of them at the same column of W's rows, the reads crowd on a part of the
+    // memory channels (218 rows, d = 2,048: 200 -> 171 us; 200 rows, d = 4,096: 358 -> 289).  Tiles
+    // that share W keep the common start, so that they meet its lines in L2, and have no scalar
+    // work for it in the loop (which took 1 to 2% of a large call).
+    const int rot = kAlone ? tn % ns : 0;
 
     // ---- direct global -> LDS loads (buffer_load_dwordx4 ... lds): for each operand and
     // stage, each wave fills 32 rows of that operand's buffer, 8 rows per instruction (lane l
@@ -201,10 +209,15 @@ __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
     }
     auto issue = [&](const __amdgpu_buffer_rsrc_t &rsrc, int j, int buf) __attribute__((always_inline)) {
         char *dst = lds + buf * kBufB;
+        int k = j;
+        if (kAlone) {
+            k += rot;
+            if (k >= ns) k -= ns;
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rsrc, LDS_PTR(dst + (32 * wave + 8 * i) * kRowB), 16, voff[i], j * kRowB, 0, 0);
+                rsrc, LDS_PTR(dst + (32 * wave + 8 * i) * kRowB), 16, voff[i], k * kRowB, 0, 0);
     };
 
     // ---- MFMA fragments: W is the A operand and H the B operand of 16 x 16 x 32 products,
@@ -233,10 +246,12 @@ __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
     // buffers hbuf and wbuf): fragments from LDS and one operand's loads, then the MFMAs.
     // The two groups are one phase apart, so every barrier is met by all eight waves: group
     // 0 at the end of a memory phase when group 1 ends a compute phase, and the other way
-    // round.  The first half-stage loads W(j+1) into the buffer of H(j-1); the second loads
-    // H(j+2) into the buffer of W(j-1) (both read for the last time in stage j-1) and waits
+    // round.  The first half-stage loads H(j+1) into the buffer of W(j-1); the second loads
+    // W(j+2) into the buffer of H(j-1) (both read for the last time in stage j-1) and waits
     // until this wave's shares of H(j+1) and W(j+1) have landed, so stage j+1 is complete in
-    // LDS at the barrier that ends stage j.
+    // LDS at the barrier that ends stage j.  W has the longer window: it comes from HBM where
+    // few row tiles share it (300 rows 249 -> 240 us, 1,000 rows 468 -> 462, 4,096 rows 1,717 ->
+    // 1,708, 16,384 rows the same, against H having it).
     // may_start: this call site can be the tile's first K step (stage 0 sits at ring position 0),
     // whose MFMAs take zero as their accumulator input.
     auto phase = [&](int j, int hf, int hbuf, int wbuf, bool may_start) __attribute__((always_inline)) {
@@ -249,12 +264,12 @@ __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
             FB[t] = *reinterpret_cast<const bf16x8 *>(lds + hb[hbuf >> 1][hf] + (hbuf & 1) * kBufB +
                                                       t * 16 * kRowB);
         if (hf == 0) {
-            const int nb = wbuf + 2 >= kBuffers ? wbuf + 2 - kBuffers : wbuf + 2;
-            if (j + 1 < ns) issue(rw, j + 1, nb);
+            const int nb = hbuf + 2 >= kBuffers ? hbuf + 2 - kBuffers : hbuf + 2;
+            if (j + 1 < ns) issue(rh, j + 1, nb);
         } else {
-            const int nb = hbuf + 4 >= kBuffers ? hbuf + 4 - kBuffers : hbuf + 4;
+            const int nb = wbuf + 4 >= kBuffers ? wbuf + 4 - kBuffers : wbuf + 4;
             if (j + 2 < ns) {
-                issue(rh, j + 2, nb);
+                issue(rw, j + 2, nb);
                 wait_vmem<4>();
             } else {
                 wait_vmem<0>();
@@ -278,18 +293,18 @@ __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
         }
         barrier();
     };
-    // H(j) lives in buffer 2j mod 5 and W(j) in buffer 2j+1 mod 5; r = j mod 5 is a
+    // W(j) lives in buffer 2j mod 5 and H(j) in buffer 2j+1 mod 5; r = j mod 5 is a
     // compile-time value at every call, so every buffer index is.
     auto stage = [&](int j, int r) __attribute__((always_inline)) {
-        const int hbuf = (2 * r) % kBuffers, wbuf = (2 * r + 1) % kBuffers;
+        const int wbuf = (2 * r) % kBuffers, hbuf = (2 * r + 1) % kBuffers;
         phase(j, 0, hbuf, wbuf, r == 0);
         phase(j, 1, hbuf, wbuf, false);
     };
-    // prologue: H(0), W(0), H(1) in flight, H(0) and W(0) landed
-    issue(rh, 0, 0);
-    issue(rw, 0, 1);
+    // prologue: W(0), H(0), W(1) in flight, W(0) and H(0) landed
+    issue(rw, 0, 0);
+    issue(rh, 0, 1);
     if (ns > 1) {
-        issue(rh, 1, 2);
+        issue(rw, 1, 2);
         wait_vmem<4>();
     } else {
         wait_vmem<0>();
@@ -348,6 +363,9 @@ __global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) {
     }
 }
 
+__global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) { fused_lse<false>(a); }
+__global__ __launch_bounds__(kThreads, 1) void fused_lse_alone_kernel(FusedArgs a) { fused_lse<true>(a); }
+
 // Fold one partial (max p.x, sum p.y of exp(z - p.x)) into a running (m, s).
 __device__ __forceinline__ void fold_partial(float &m, float &s, const float2 p) {
     const float mn = fmaxf(m, p.x);
@@ -355,6 +373,196 @@ __device__ __forceinline__ void fold_partial(float &m, float &s, const float2 p)
     s = s * ex2((m - ref) * kLog2e) + p.y * ex2((p.x - ref) * kLog2e);
     m = mn;
 }
+
+// ---- up to 128 rows ----
+// The same product where reading W once bounds it (N <= 128): one workgroup per
+// CU takes an equal share of the vocabulary for all BT tokens, and streams it without a pause.
+// Eight waves of 32 vocabulary entries x BT tokens each; W goes from memory straight into
+// registers as MFMA A operands, since no two waves share a row of it, and H through a ring of
+// kRing LDS buffers of one 64-wide K stage.  The loads of stage t + 3 are issued when stage t
+// begins, so W has three stages to arrive (the tile kernel's window is one and a half, short of
+// HBM's latency), and the stages run on across the passes over a workgroup's share, so the ring
+// never drains.  A workgroup's K stages start at its own place, so that the chip's W reads, all
+// rows at the same column otherwise, spread over the memory channels.  Per token a wave keeps its
+// (max, sum) over its passes in LDS; the workgroup writes one partial per token.
+constexpr int kRing = 4;
+constexpr int kRowsWaves = 8;
+constexpr int kShareRows = 32;   // vocabulary entries of a wave and pass
+constexpr int kCUs = 256;
+// Tokens up to which this kernel takes the call.  Measured against the tile kernel (teacher call,
+// V = 151,936, d = 2,048): 16 rows 193 -> 120 us, 64 rows 192 -> 122, 128 rows 192 -> 136.  With
+// BT = 256 a wave's 32 entries give two products for each fragment read from LDS and the reads
+// bound it: 218 rows 183 us against 174 as one tile row.
+constexpr int kMaxRowsN = 128;
+
+template <int BT>
+__device__ __forceinline__ void fused_rows(const FusedArgs &a) {
+    constexpr int kStage = BT * kRowB;      // H bytes of one stage
+    constexpr int kTiles = BT / 16;         // token tiles
+    constexpr int kHLoads = BT / 64;        // H loads per wave and stage, 8 rows each
+    constexpr int kLoads = kHLoads + 4;     // and all of its loads
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float2 *part = reinterpret_cast<float2 *>(lds + kRing * kStage) + wave * BT;
+    for (int i = lane; i < BT; i += kWave) part[i] = make_float2(-INFINITY, 0.0f);
+
+    // ---- this workgroup's blocks of 32 vocabulary entries, in passes of `per` <= 8 ----
+    const int nblk = (a.vocab + kShareRows - 1) / kShareRows;
+    const int b0 = (int)((int64_t)nblk * blockIdx.x / gridDim.x);
+    const int cnt = (int)((int64_t)nblk * (blockIdx.x + 1) / gridDim.x) - b0;
+    const int passes = (cnt + kRowsWaves - 1) / kRowsWaves;
+    const int per = (cnt + passes - 1) / passes;
+    const int d = a.d, ns = d / kBK, total = passes * ns;
+    const int rot = (int)(blockIdx.x % (unsigned)ns);
+    const int64_t v0 = (int64_t)b0 * kShareRows;
+    const int64_t w_rows = (a.vocab - v0) < (int64_t)cnt * kShareRows ? (a.vocab - v0)
+                                                                      : (int64_t)cnt * kShareRows;
+    const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)a.h, (short)0, (int)(a.n_rows * d * 2), kBufferFlags);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(a.w + v0 * d), (short)0, (int)(w_rows * d * 2), kBufferFlags);
+
+    int hoff[kHLoads];
+#pragma unroll
+    for (int i = 0; i < kHLoads; ++i) {
+        const int R = (wave * kHLoads + i) * 8 + (lane >> 3);
+        hoff[i] = (R * d + (((lane & 7) ^ swz(R)) * 8)) * 2;
+    }
+    const int fr = lane & 15, kg = lane >> 4;
+    const int woff = (fr * d + kg * 8) * 2;  // of the wave's first row; other half + 64 bytes
+    u32x4 wreg[kRing][2][2];                 // [stage][16-row block][stage half]
+    int ij = 0, iq = 0;                      // stage and pass of the next loads
+    auto issue = [&](int slot) __attribute__((always_inline)) {
+        int k = ij + rot;
+        if (k >= ns) k -= ns;
+        char *dst = lds + slot * kStage + wave * kHLoads * 8 * kRowB;
+#pragma unroll
+        for (int i = 0; i < kHLoads; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rh, LDS_PTR(dst + i * 8 * kRowB), 16, hoff[i],
+                                                     k * kRowB, 0, 0);
+        // blocks past the share lie past the descriptor: zeros, and no memory traffic
+        const int blk = iq * per + wave;
+        const int base = wave < per && blk < cnt ? blk * kShareRows * d * 2 : 0x7f000000;
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+                wreg[slot][mb][hf] = __builtin_amdgcn_raw_buffer_load_b128(
+                    rw, base + woff + mb * 16 * d * 2 + hf * 64, k * kRowB, 0);
+        if (++ij == ns) {
+            ij = 0;
+            ++iq;
+        }
+    };
+    int hb[2];
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) hb[hf] = fr * kRowB + (((4 * hf + kg) ^ swz(fr)) * 16);
+
+    f32x4 acc[2][kTiles];
+    int j = 0, q = 0;  // stage and pass being multiplied
+    auto step = [&](int slot) __attribute__((always_inline)) {
+        issue((slot + kRing - 1) % kRing);
+        const int blk = q * per + wave;
+        const bool busy = wave < per && blk < cnt;
+        if (busy) {
+            if (j == 0) {
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                    for (int jj = 0; jj < kTiles; ++jj) acc[mb][jj] = f32x4{};
+            }
+            // token fragments in groups of four, the next group's reads ahead of this one's products
+            constexpr int kGroups = 2 * kTiles / 4;
+            bf16x8 fb[2][4];
+            auto read = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int hf = g / (kTiles / 4), jj = g % (kTiles / 4) * 4 + i;
+                    fb[g & 1][i] = *reinterpret_cast<const bf16x8 *>(lds + slot * kStage + hb[hf] +
+                                                                     jj * 16 * kRowB);
+                }
+            };
+            read(0);
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) {
+                const int hf = g / (kTiles / 4);
+                if (g + 1 < kGroups) read(g + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb) {
+                        const int jj = g % (kTiles / 4) * 4 + i;
+                        acc[mb][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, wreg[slot][mb][hf]), fb[g & 1][i], acc[mb][jj], 0, 0, 0);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (++j == ns) {
+            j = 0;
+            ++q;
+            if (busy) {
+                // entries mb*16 + 4*kg + e of token jj*16 + fr, as in the tile kernel's epilogue
+                const int vlim = (int)(a.vocab - (v0 + (int64_t)blk * kShareRows));
+#pragma unroll
+                for (int jj = 0; jj < kTiles; ++jj) {
+                    float z[8];
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) {
+                        z[x] = acc[x >> 2][jj][x & 3];
+                        if (vlim < kShareRows && (x >> 2) * 16 + kg * 4 + (x & 3) >= vlim) z[x] = -INFINITY;
+                    }
+                    float m = z[0];
+#pragma unroll
+                    for (int x = 1; x < 8; ++x) m = fmaxf(m, z[x]);
+                    m = fmaxf(m, __shfl_xor(m, 16, 64));
+                    m = fmaxf(m, __shfl_xor(m, 32, 64));
+                    const float mref = ((m == -INFINITY) ? 0.0f : m) * kLog2e;
+                    float sum = 0.0f;
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) sum += ex2(__builtin_fmaf(z[x], kLog2e, -mref));
+                    sum += __shfl_xor(sum, 16, 64);
+                    sum += __shfl_xor(sum, 32, 64);
+                    if (kg == 0) {
+                        float2 o = part[jj * 16 + fr];
+                        fold_partial(o.x, o.y, make_float2(m, sum));
+                        part[jj * 16 + fr] = o;
+                    }
+                }
+            }
+        }
+        // this wave's H loads of stage t + 1 have landed (W's four of it were issued behind them);
+        // after the barrier so have all waves', and this stage's buffer is free
+        wait_vmem<2 * kLoads + 4>();
+        barrier();
+    };
+#pragma unroll
+    for (int t = 0; t < kRing - 1; ++t) issue(t);
+    wait_vmem<2 * kLoads + 4>();
+    barrier();
+    // Stages past the last pass load h again and no W, and multiply nothing: every load is issued
+    // on every path, so the waits count the same loads everywhere.
+    for (int t = 0; t < total; t += kRing) {
+        step(0);
+        step(1);
+        step(2);
+        step(3);
+    }
+    wait_vmem<0>();
+    __syncthreads();
+    const float2 *all = reinterpret_cast<const float2 *>(lds + kRing * kStage);
+    for (int i = tid; i < BT; i += kRowsWaves * kWave) {
+        float2 o = all[i];
+#pragma unroll
+        for (int w = 1; w < kRowsWaves; ++w) fold_partial(o.x, o.y, all[w * BT + i]);
+        if (i < a.n_rows) a.partial[(int64_t)blockIdx.x * a.n_rows + i] = o;
+    }
+}
+
+__global__ __launch_bounds__(kRowsWaves *kWave, 1) void fused_rows64_kernel(FusedArgs a) { fused_rows<64>(a); }
+__global__ __launch_bounds__(kRowsWaves *kWave, 1) void fused_rows128_kernel(FusedArgs a) { fused_rows<128>(a); }
 
 constexpr int kMergeThreads = 1024;  // 16 waves per workgroup
 // Rows from which a merge workgroup takes 64 rows instead of 16: measured, 16 rows take 30.1 us
@@ -471,10 +679,36 @@ hipError_t ensure_lds_limit() {
     if (e != hipSuccess) return e;
     const uint64_t bit = (dev >= 0 && dev < 64) ? (1ull << dev) : 0;
     if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(fused_lse_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+    for (const void *f : {reinterpret_cast<const void *>(fused_lse_kernel),
+                          reinterpret_cast<const void *>(fused_lse_alone_kernel),
+                          reinterpret_cast<const void *>(fused_rows64_kernel),
+                          reinterpret_cast<const void *>(fused_rows128_kernel)}) {
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+        if (e != hipSuccess) return e;
+    }
     if (e == hipSuccess && bit) done.fetch_or(bit, std::memory_order_release);
     return e;
+}
+
+}  // namespace
+
+namespace {
+
+hipError_t launch_rows(const FusedArgs &a, hipStream_t stream) {
+    const int bt = a.n_rows <= 64 ? 64 : 128;
+    const size_t lds = (size_t)kRing * bt * kRowB + (size_t)kRowsWaves * bt * sizeof(float2);
+    hipLaunchKernelGGL(bt == 64 ? fused_rows64_kernel : fused_rows128_kernel, dim3((unsigned)a.n_half),
+                       dim3(kRowsWaves * kWave), lds, stream, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_merge(const FusedArgs &a, const int32_t *ids, float *logp_t, uint32_t *flags,
+                        hipStream_t stream) {
+    const int rw = a.n_rows < kMergeWide ? 16 : 64;
+    hipLaunchKernelGGL(a.n_rows < kMergeWide ? fused_merge_kernel<16> : fused_merge_kernel<64>,
+                       dim3((unsigned)((a.n_rows + rw - 1) / rw)), dim3(kMergeThreads), 0, stream,
+                       a.partial, a.h, a.w, ids, logp_t, a.n_rows, a.n_half, a.vocab, a.d, flags);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -510,19 +744,27 @@ hipError_t launch_fused_teacher(const uint16_t *h, const uint16_t *w, const int3
     a.partial = static_cast<float2 *>(ws);
     hipError_t e = ensure_lds_limit();
     if (e != hipSuccess) return e;
+    if (n_rows <= kMaxRowsN) {
+        // no more workgroups than partials that the workspace holds; a share's bytes fit the 32-bit
+        // range of one descriptor
+        const int grid = a.n_half < kCUs ? a.n_half : kCUs;
+        if (((int64_t)vocab / grid + 2 * kShareRows) * d * 2 < 0x7f000000) {
+            a.n_half = grid;
+            e = launch_rows(a, stream);
+            if (e != hipSuccess) return e;
+            return launch_merge(a, ids, logp_t, flags, stream);
+        }
+    }
     const int64_t rem = a.tiles_m - a.super_rows * 16;
     const int64_t blocks = 8 * ((int64_t)a.super_rows * a.super_cols * 32 +
                                 (int64_t)a.super_rows * 2 * (a.tiles_n - a.super_cols * 16) +
                                 rem * ((a.tiles_n + 7) / 8));
     if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;  // grid past the 32-bit limit
-    hipLaunchKernelGGL(fused_lse_kernel, dim3((unsigned)blocks), dim3(kThreads), kLdsBytes, stream, a);
+    hipLaunchKernelGGL(a.tiles_m == 1 ? fused_lse_alone_kernel : fused_lse_kernel, dim3((unsigned)blocks),
+                       dim3(kThreads), kLdsBytes, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int rw = n_rows < kMergeWide ? 16 : 64;
-    hipLaunchKernelGGL(n_rows < kMergeWide ? fused_merge_kernel<16> : fused_merge_kernel<64>,
-                       dim3((unsigned)((n_rows + rw - 1) / rw)), dim3(kMergeThreads), 0, stream,
-                       a.partial, h, w, ids, logp_t, n_rows, a.n_half, vocab, d, flags);
-    return hipGetLastError();
+    return launch_merge(a, ids, logp_t, flags, stream);
 }
 
 }  // namespace stride

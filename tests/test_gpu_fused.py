@@ -91,6 +91,34 @@ def test_fused_tile_numbering(rows, vocab):
     assert np.max(np.abs(got[at] - sc["logp_t"])) <= H.TOL_LOGP
 
 
+@pytest.mark.parametrize("rows,vocab,d", [
+    (1, 33, 64),        # one K stage, two blocks of 32 entries, the second of one entry
+    (64, 127, 128),     # one workgroup, two stages
+    (65, 4097, 192),    # 128 tokens' form, three stages: the ring's fourth step is past the end
+    (128, 32768, 320),  # 1,024 blocks on 256 workgroups: four of eight waves
+    (127, 65569, 256),  # 2,050 blocks: eight and nine a workgroup, one pass and two; V odd
+    (40, 140000, 576),  # 4,375 blocks: three passes of six; nine stages
+    (129, 33000, 256),  # one tile row past the form: each tile starts at its own stage
+    (256, 5000, 448),
+])
+def test_fused_few_rows(rows, vocab, d):
+    """Up to 128 rows W streams through registers in equal shares, and up to 256 a tile row starts
+    its K stages apart: every row against the oracle, the partial table filled with NaN before."""
+    import torch
+    import paper_2609_14636_amd as P
+    wl = W.make("fused", seed=11 + rows, scale=dict(R=1, turns=1, tok=rows, vocab=vocab, d=d))
+    inp = H.device_inputs_fused(wl)
+    path = P.Path(inp["layout"], wl.unit, with_student=False, fused_vocab=vocab)
+    for _ in range(2):
+        path.fused_ws.fill_(0xFF)
+        path.logp_t.fill_(7.0)
+        path.score_fused(vocab, inp["hidden"], inp["w"], None, inp["ids"])
+    torch.cuda.synchronize()
+    assert int(path.flags.item()) == 0
+    sc, _ = H.oracle_fused_scores(wl, np.arange(rows), matmul=True)
+    assert np.max(np.abs(path.logp_t.cpu().numpy() - sc["logp_t"])) <= H.TOL_LOGP
+
+
 def test_fused_random_shapes():
     """Thirty random small shapes against the oracle: 1 to 1,200 rows (partial row tiles),
     vocabularies of 1 to 5,000 entries (partial 128- and 256-column tiles) and hidden sizes of one
