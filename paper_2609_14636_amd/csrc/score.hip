@@ -22,12 +22,6 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.69314718055994531f;
 constexpr uint8_t kBadDomain = 0xFF;
-constexpr int kSplitWaves = 8;  // wavefronts that share a token's two rows in the paired pass
-// Tokens below which the paired pass (exact KL) shares each token's two rows the same way:
-// measured, the shared form is as fast or faster up to 65,536 tokens (64 tokens: 25 us against
-// 108 us) and 0.7-1.4% slower at 85,185 and 131,072.
-constexpr int64_t kPairSplitBelow = 65536;
-
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int DT>
@@ -276,7 +270,7 @@ __global__ __launch_bounds__(W *RW *kWave) void score_rows_kernel(ScoreArgs a) {
     if (lane == 0) write_row(a, row, y, xy, m, s, out);
 }
 
-// Exact reverse KL in the same pass: one wavefront per token streams the teacher
+// Exact reverse KL in the same pass: a token's wavefronts stream the teacher
 // and the student row together.  With p_S(v) = exp(s_v - LSE_S),
 //   KL(pi_S || pi_T) = sum_v p_S(v) (s_v - t_v) - LSE_S + LSE_T
 //                    = A / Z_S - LSE_S + LSE_T,  A = sum_v exp(s_v - m_S) (s_v - t_v),
@@ -349,12 +343,11 @@ __device__ __forceinline__ void pair_wave_merge(float &mt, float &zt, float &ms,
     }
 }
 
-// The token's exact KL and both sampled-token log-probabilities from the merged states.
-template <int DT>
-__device__ __forceinline__ void write_pair(const PairArgs &a, int64_t row, const u32x4 *pt,
-                                           const u32x4 *ps, float mt, float zt, float ms, float zs,
+// The token's exact KL and both sampled-token log-probabilities from the merged states and the
+// sampled logits.
+__device__ __forceinline__ void write_pair(const PairArgs &a, int64_t row, int32_t y, float xt,
+                                           float xs, float mt, float zt, float ms, float zs,
                                            float am) {
-    const int32_t y = a.ids[row];
     uint32_t bad = 0;
     const bool fin_t = (mt > -INFINITY) && (mt < INFINITY) && (zt > 0.0f) && (zt < INFINITY);
     const bool fin_s = (ms > -INFINITY) && (ms < INFINITY) && (zs > 0.0f) && (zs < INFINITY);
@@ -373,14 +366,6 @@ __device__ __forceinline__ void write_pair(const PairArgs &a, int64_t row, const
     if (bad & (STRIDE_FLAG_TOKEN_OOB | (fin_t && fin_s ? 0u : STRIDE_FLAG_NONFINITE))) {
         rt = rs = __builtin_nanf("");
     } else {
-        float xt, xs;
-        if (DT == STRIDE_BF16) {
-            xt = __uint_as_float((uint32_t)(reinterpret_cast<const uint16_t *>(pt)[y]) << 16);
-            xs = __uint_as_float((uint32_t)(reinterpret_cast<const uint16_t *>(ps)[y]) << 16);
-        } else {
-            xt = reinterpret_cast<const float *>(pt)[y];
-            xs = reinterpret_cast<const float *>(ps)[y];
-        }
         rt = fminf((xt - mt) - lt, 0.0f);  // at most 0, as in score_rows_kernel
         rs = fminf((xs - ms) - ls, 0.0f);
     }
@@ -389,15 +374,23 @@ __device__ __forceinline__ void write_pair(const PairArgs &a, int64_t row, const
     a.logp_s[row] = rs;
 }
 
-template <int DT, int U>
-__global__ __launch_bounds__(256) void score_pairs_kernel(PairArgs a) {
+// W wavefronts share a token's two rows, RW tokens per workgroup, D chunks of U loads of each row per
+// wavefront, as in score_rows_kernel; the five-value states are merged in wavefront order.  The
+// two exponentials and eleven other instructions per pair of entries keep the vector units busy
+// for most of the time that HBM takes, so fewer wavefronts than for single rows pay.
+template <int DT, int W, int RW, int U, int D>
+__global__ __launch_bounds__(W *RW *kWave) void score_pairs_kernel(PairArgs a) {
+    static_assert(W == 1 || RW == 1, "wavefronts that share a token meet at a workgroup barrier");
     constexpr int E = Elem<DT>::kPerVec;
+    __shared__ float s_st[5][W], s_x[2];
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-    if (row >= a.n_rows) return;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wave = W == 1 ? 0 : wid;
+    const int64_t row = (int64_t)blockIdx.x * RW + (W == 1 ? wid : 0);
+    if (row >= a.n_rows) return;  // W > 1: never, the grid has exactly n_rows workgroups
     const int d = a.row_dom ? (int)a.row_dom[row] : 0;
-    if (d >= a.n_teachers) {
-        if (lane == 0) {
+    if (d >= a.n_teachers) {  // the same for the token's wavefronts: they leave before any barrier
+        if (wave == 0 && lane == 0) {
             a.logp_t[row] = __builtin_nanf("");
             a.kl_full[row] = __builtin_nanf("");
             a.logp_s[row] = __builtin_nanf("");
@@ -407,100 +400,77 @@ __global__ __launch_bounds__(256) void score_pairs_kernel(PairArgs a) {
     const size_t off = (size_t)row * a.ld * Elem<DT>::kSize;
     const u32x4 *pt = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.teachers.p[d]) + off);
     const u32x4 *ps = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.student) + off);
-    const int64_t nvec = a.vocab / E;
+    const int32_t y = a.ids[row];
+    const int nvec = a.vocab / E;
     const int tail = a.vocab % E;
+    constexpr int kStep = U * kWave;
+    const int nfull = nvec / kStep;
+    const int mine = nfull > wave ? (nfull - wave + W - 1) / W : 0;
     float mt = -INFINITY, zt = 0.0f, ms = -INFINITY, zs = 0.0f, am = 0.0f;
-    int64_t k = 0;
-    constexpr int64_t kStep = (int64_t)U * kWave;
-    for (; k + kStep <= nvec; k += kStep) {
-        u32x4 vt[U], vs[U];
+    struct Chunk {
+        u32x4 t[U], s[U];
+    };
+    auto load = [&](int i, Chunk &v) __attribute__((always_inline)) {
+        const int64_t k = (int64_t)(wave + i * W) * kStep + lane;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            vt[u] = __builtin_nontemporal_load(pt + k + u * kWave + lane);
-            vs[u] = __builtin_nontemporal_load(ps + k + u * kWave + lane);
+            v.t[u] = __builtin_nontemporal_load(pt + k + u * kWave);
+            v.s[u] = __builtin_nontemporal_load(ps + k + u * kWave);
         }
+    };
+    auto use = [&](const Chunk &v) __attribute__((always_inline)) {
         float xt[U * E], xs[U * E];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            unpack<DT>(vt[u], xt + u * E);
-            unpack<DT>(vs[u], xs + u * E);
+            unpack<DT>(v.t[u], xt + u * E);
+            unpack<DT>(v.s[u], xs + u * E);
         }
         fold_pair<U * E>(mt, zt, ms, zs, am, xt, xs);
-    }
-    for (; k < nvec; k += kWave) {
-        if (k + lane < nvec) {
-            float xt[E], xs[E];
-            unpack<DT>(__builtin_nontemporal_load(pt + k + lane), xt);
-            unpack<DT>(__builtin_nontemporal_load(ps + k + lane), xs);
-            fold_pair<E>(mt, zt, ms, zs, am, xt, xs);
+    };
+    // words after the last whole chunk, every W-th block of 64 of them
+    constexpr int kRest = (U + W - 1) / W;
+    u32x4 rest_t[kRest], rest_s[kRest];
+#pragma unroll
+    for (int i = 0; i < kRest; ++i) {
+        const int k = nfull * kStep + (i * W + wave) * kWave + lane;
+        constexpr uint32_t n = Elem<DT>::kNegInf;
+        rest_t[i] = rest_s[i] = u32x4{n, n, n, n};
+        if (k < nvec) {
+            rest_t[i] = __builtin_nontemporal_load(pt + k);
+            rest_s[i] = __builtin_nontemporal_load(ps + k);
         }
     }
-    if (tail && lane == 0) {
-        float xt[E], xs[E];
-        unpack<DT>(pt[nvec], xt);
-        unpack<DT>(ps[nvec], xs);
+    Chunk v[D];
+    if (D == 1) {
+        for (int i = 0; i < mine; ++i) {
+            load(i, v[0]);
+            use(v[0]);
+        }
+    } else {
 #pragma unroll
-        for (int j = 0; j < E; ++j)
-            if (j >= tail) {
-                xt[j] = -INFINITY;
-                xs[j] = -INFINITY;
+        for (int q = 0; q < D - 1; ++q)
+            if (q < mine) load(q, v[q]);
+        int i = 0;
+        for (; i + 2 * D - 2 < mine; i += D) {
+#pragma unroll
+            for (int q = 0; q < D; ++q) {
+                load(i + q + D - 1, v[(q + D - 1) % D]);
+                use(v[q]);
             }
+        }
+        // at most 2 D - 2 chunks left, the first D - 1 of them in flight
+#pragma unroll
+        for (int q = 0; q < 2 * D - 2; ++q) {
+            if (i + q + D - 1 < mine) load(i + q + D - 1, v[(q + D - 1) % D]);
+            if (i + q < mine) use(v[q % D]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kRest; ++i) {
+        float xt[E], xs[E];
+        unpack<DT>(rest_t[i], xt);
+        unpack<DT>(rest_s[i], xs);
         fold_pair<E>(mt, zt, ms, zs, am, xt, xs);
-    }
-    pair_wave_merge(mt, zt, ms, zs, am);
-    if (lane == 0) write_pair<DT>(a, row, pt, ps, mt, zt, ms, zs, am);
-}
-
-// The paired pass for small batches, as score_rows_split_kernel does for single rows: the
-// kSplitWaves wavefronts of a workgroup share one token's teacher and student rows (chunks w,
-// w + kSplitWaves, ...) and merge their five-value states in wavefront order through LDS.
-template <int DT, int U>
-__global__ __launch_bounds__(kSplitWaves *kWave) void score_pairs_split_kernel(PairArgs a) {
-    constexpr int E = Elem<DT>::kPerVec;
-    __shared__ float s_st[5][kSplitWaves];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int64_t row = blockIdx.x;  // one workgroup per token: the grid has exactly n_rows
-    const int d = a.row_dom ? (int)a.row_dom[row] : 0;
-    if (d >= a.n_teachers) {  // the same for the whole workgroup: it leaves before any barrier
-        if (threadIdx.x == 0) {
-            a.logp_t[row] = __builtin_nanf("");
-            a.kl_full[row] = __builtin_nanf("");
-            a.logp_s[row] = __builtin_nanf("");
-        }
-        return;
-    }
-    const size_t off = (size_t)row * a.ld * Elem<DT>::kSize;
-    const u32x4 *pt = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.teachers.p[d]) + off);
-    const u32x4 *ps = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.student) + off);
-    const int64_t nvec = a.vocab / E;
-    const int tail = a.vocab % E;
-    constexpr int64_t kStep = (int64_t)U * kWave;
-    const int64_t nfull = nvec / kStep;
-    float mt = -INFINITY, zt = 0.0f, ms = -INFINITY, zs = 0.0f, am = 0.0f;
-    for (int64_t c = wave; c < nfull; c += kSplitWaves) {
-        const int64_t k = c * kStep;
-        u32x4 vt[U], vs[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            vt[u] = __builtin_nontemporal_load(pt + k + u * kWave + lane);
-            vs[u] = __builtin_nontemporal_load(ps + k + u * kWave + lane);
-        }
-        float xt[U * E], xs[U * E];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            unpack<DT>(vt[u], xt + u * E);
-            unpack<DT>(vs[u], xs + u * E);
-        }
-        fold_pair<U * E>(mt, zt, ms, zs, am, xt, xs);
-    }
-    for (int64_t k = nfull * kStep + (int64_t)wave * kWave; k < nvec; k += (int64_t)kSplitWaves * kWave) {
-        if (k + lane < nvec) {
-            float xt[E], xs[E];
-            unpack<DT>(__builtin_nontemporal_load(pt + k + lane), xt);
-            unpack<DT>(__builtin_nontemporal_load(ps + k + lane), xs);
-            fold_pair<E>(mt, zt, ms, zs, am, xt, xs);
-        }
     }
     if (tail && wave == 0 && lane == 0) {
         float xt[E], xs[E];
@@ -514,20 +484,33 @@ __global__ __launch_bounds__(kSplitWaves *kWave) void score_pairs_split_kernel(P
             }
         fold_pair<E>(mt, zt, ms, zs, am, xt, xs);
     }
+    float yt = 0.0f, ys = 0.0f;  // the sampled logits: the last wavefront has the fewest chunks
+    if (wave == W - 1 && y >= 0 && y < a.vocab) {
+        yt = element<DT>(pt, y);
+        ys = element<DT>(ps, y);
+    }
     pair_wave_merge(mt, zt, ms, zs, am);
-    if (lane == 0) {
-        s_st[0][wave] = mt;
-        s_st[1][wave] = zt;
-        s_st[2][wave] = ms;
-        s_st[3][wave] = zs;
-        s_st[4][wave] = am;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {  // wave 0's state, then waves 1, 2, ... in order
-        for (int w = 1; w < kSplitWaves; ++w)
+    if (W > 1) {
+        if (lane == 0) {
+            s_st[0][wave] = mt;
+            s_st[1][wave] = zt;
+            s_st[2][wave] = ms;
+            s_st[3][wave] = zs;
+            s_st[4][wave] = am;
+            if (wave == W - 1) {
+                s_x[0] = yt;
+                s_x[1] = ys;
+            }
+        }
+        __syncthreads();
+        if (wave != 0) return;
+        yt = s_x[0];
+        ys = s_x[1];
+#pragma unroll
+        for (int w = 1; w < W; ++w)
             pair_merge(mt, zt, ms, zs, am, s_st[0][w], s_st[1][w], s_st[2][w], s_st[3][w], s_st[4][w]);
-        write_pair<DT>(a, row, pt, ps, mt, zt, ms, zs, am);
     }
+    if (lane == 0) write_pair(a, row, y, yt, ys, mt, zt, ms, zs, am);
 }
 
 // Teacher index of every row: row -> turn (by offsets) -> rollout -> domain.
@@ -611,6 +594,29 @@ hipError_t launch_rows(const ScoreArgs &a, hipStream_t stream) {
     return launch_rows_form<DT, 8, 1, 4, 3>(a, stream);
 }
 
+template <int DT, int W, int RW, int U, int D>
+hipError_t launch_pairs_form(const PairArgs &a, hipStream_t stream) {
+    hipLaunchKernelGGL((score_pairs_kernel<DT, W, RW, U, D>), dim3((unsigned)((a.n_rows + RW - 1) / RW)),
+                       dim3(W * RW * kWave), 0, stream, a);
+    return hipGetLastError();
+}
+
+// The form by the row's 16-byte words and the number of tokens, as for single rows.  bf16, eight
+// wavefronts with one chunk in flight for every length -> the form taken here:
+//   words  125, 30,000 tokens: 199 -> 32 us; words 500: 299 -> 78
+//   words 1,500, 30,000 tokens: 383 -> 220 us; words 4,000: 638 -> 564
+//   words 12,500, 5,000 tokens: 303 -> 298 us (four wavefronts 304)
+//   words 18,992: 64 tokens 23 us either way (four 28), 16,384 tokens 1,434 -> 1,422, 60,000 tokens
+//                 5,210 -> 5,165 (one wavefront per token 5,287)
+template <int DT>
+hipError_t launch_pairs(const PairArgs &a, hipStream_t stream) {
+    const int words = a.vocab / Elem<DT>::kPerVec;
+    if (words < 1024) return launch_pairs_form<DT, 1, 4, 2, 1>(a, stream);
+    if (words < 5120) return launch_pairs_form<DT, 4, 1, 4, 1>(a, stream);
+    if (a.n_rows >= 16384) return launch_pairs_form<DT, 4, 1, 4, 2>(a, stream);
+    return launch_pairs_form<DT, 8, 1, 4, 1>(a, stream);
+}
+
 }  // namespace
 
 hipError_t launch_score_pairs(int32_t dtype, const PtrTable &teachers, int32_t n_teachers,
@@ -631,23 +637,8 @@ hipError_t launch_score_pairs(int32_t dtype, const PtrTable &teachers, int32_t n
     a.ld = ld;
     a.vocab = vocab;
     a.n_teachers = n_teachers;
-    if (n_rows < kPairSplitBelow) {
-        if (dtype == STRIDE_BF16)
-            hipLaunchKernelGGL((score_pairs_split_kernel<STRIDE_BF16, 4>), dim3((unsigned)n_rows),
-                               dim3(kSplitWaves * kWave), 0, stream, a);
-        else
-            hipLaunchKernelGGL((score_pairs_split_kernel<STRIDE_F32, 4>), dim3((unsigned)n_rows),
-                               dim3(kSplitWaves * kWave), 0, stream, a);
-        return hipGetLastError();
-    }
-    const int64_t blocks = (n_rows + 3) / 4;
-    if (dtype == STRIDE_BF16)
-        hipLaunchKernelGGL((score_pairs_kernel<STRIDE_BF16, 4>), dim3((unsigned)blocks), dim3(256), 0,
-                           stream, a);
-    else
-        hipLaunchKernelGGL((score_pairs_kernel<STRIDE_F32, 4>), dim3((unsigned)blocks), dim3(256), 0,
-                           stream, a);
-    return hipGetLastError();
+    if (dtype == STRIDE_BF16) return launch_pairs<STRIDE_BF16>(a, stream);
+    return launch_pairs<STRIDE_F32>(a, stream);
 }
 
 hipError_t launch_row_domain(const stride_layout &L, int32_t n_teachers, uint8_t *row_dom,

@@ -13,6 +13,54 @@ FEW = [1, 63, 65, 255, 256, 257, 1023, 1024, 1025, 2047, 3071, 3072, 3073, 4095,
 MANY = [8192, 8703, 16384, 16999, 20480, 24575, 24576]
 
 
+PAIR_WORDS = [1, 127, 129, 1000, 1023, 1024, 1279, 2500, 5119, 5120, 7000]
+
+
+def _check_pairs(words, n, dtype, pad):
+    import torch
+    import paper_2609_14636_amd as P
+    per = 8 if dtype is torch.bfloat16 else 4
+    vocab = words * per + pad
+    ld = vocab + (-vocab) % per
+    g = torch.Generator(device="cuda").manual_seed(words + n)
+    t, s = (torch.empty((n, ld), dtype=dtype, device="cuda").normal_(0, 3, generator=g) for _ in range(2))
+    ids = torch.randint(0, vocab, (n,), dtype=torch.int32, device="cuda", generator=g)
+    ids[0] = vocab - 1
+    t[:, vocab:] = 900.0
+    s[:, vocab:] = 1000.0
+    if vocab > 4:
+        t[2, 2::3] = s[2, 2::3] = -math.inf     # no mass on either side
+        s[3, 2::3] = -math.inf                  # the teacher alone has some
+        t[1, 2::3] = -math.inf                  # the student alone: the divergence is infinite
+        ids[1:4] = 0
+    s[4, vocab // 2] = math.nan
+    ids[6] = vocab
+    lay = P.Layout(torch.tensor([0, 1], dtype=torch.int32, device="cuda"),
+                   torch.tensor([0, n], dtype=torch.int64, device="cuda"), n)
+    path = P.Path(lay, P.STRIDE_UNIT_TURN, exact_kl=True)
+    path.score(vocab, [t], s, ids)
+    assert torch.isnan(path.kl_full[4]) and torch.isnan(path.logp_s[4])
+    assert torch.isnan(path.logp_t[6]) and torch.isfinite(path.kl_full[6])
+    at = torch.tensor([0, 2, 3] + list(range(8, n, max(1, n // 64))) + [n - 1], device="cuda")
+    lt, ls = (x[at][:, :vocab].double().log_softmax(1) for x in (t, s))
+    pick = ids[at].long().unsqueeze(1)
+    kl = torch.where(ls > -math.inf, ls.exp() * (ls - lt), torch.zeros_like(ls)).sum(1)
+    for got, want in ((path.logp_t, lt.gather(1, pick).squeeze(1)), (path.logp_s, ls.gather(1, pick).squeeze(1))):
+        assert float((got[at].double() - want).abs().max()) <= 2e-5
+    # a sum of p (s - t) of size about 10 and two logarithms, in fp32
+    assert float((path.kl_full[at].double() - kl).abs().max()) <= 1e-4
+    assert vocab <= 4 or float(path.kl_full[1]) == math.inf
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_pairs(dtype):
+    import torch
+    for n in (24, 16384 + 3):
+        for words in PAIR_WORDS:
+            print("words", words, "tokens", n, flush=True)
+            _check_pairs(words, n, torch.bfloat16 if dtype == "bf16" else torch.float32, 3)
+
+
 def _check(words, n, dtype, pad):
     import torch
     import paper_2609_14636_amd as P
