@@ -8,7 +8,7 @@
 // log-normaliser comes for free from the scoring pass: LSE_S = s_y - log pi_S(y),
 // so p_S(v) = exp(s_v - s_y + log pi_S(y)).
 //
-// Eight wavefronts per row stream the student row once (16-byte non-temporal
+// A row's wavefronts stream the student row once (16-byte non-temporal
 // loads) and write the gradient row once; a row that is not retained is
 // written as zeros without being read.  Columns ld - vocab of padding are not
 // touched.  A small kernel first marks the retained rows.
@@ -18,10 +18,6 @@ namespace stride {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-// Wavefronts per row.  Measured against one wavefront per row on V = 151,936 bf16 rows (gradient
-// bits equal): eight are faster at every batch size, 26% at 1,024 rows and 4.4% at 131,072
-// (14.94 against 15.62 ms for the whole read + write of 79.7 GB).
-constexpr int kGradWaves = 8;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -92,17 +88,20 @@ struct GradArgs {
     float scale;
 };
 
-// One row per workgroup of W = kGradWaves wavefronts: wavefront w handles the row's U-load chunks
-// w, w + W, ... and every W-th word after the last whole chunk.  Every element's gradient depends
-// only on that element, so nothing is merged and the bits do not depend on the split.
-template <int DT>
-__global__ __launch_bounds__(kGradWaves *kWave) void opd_grad_kernel(GradArgs a) {
+// W wavefronts per row, RW rows per workgroup: wavefront w handles the row's U-load chunks w, w + W, ...
+// and every W-th word after the last whole chunk.  Every element's gradient depends only on that
+// element, so nothing is merged and the bits do not depend on the split.  HBM bounds it (a read
+// and a write stream); the row's first loads are issued before the sampled logit's two dependent
+// ones are waited for.  launch_form has the choice of W and what it measured.
+template <int DT, int W, int RW>
+__global__ __launch_bounds__(W *RW *kWave) void opd_grad_kernel(GradArgs a) {
+    static_assert(W == 1 || RW == 1, "a workgroup holds one row or one wavefront of each");
     constexpr int E = (DT == STRIDE_BF16) ? 8 : 4;
     constexpr int ES = (DT == STRIDE_BF16) ? 2 : 4;
-    constexpr int W = kGradWaves;
     const int lane = threadIdx.x & (kWave - 1);
-    const int sub = threadIdx.x / kWave;  // this wavefront's share of the row
-    const int64_t row = blockIdx.x;       // the grid has exactly n_rows workgroups
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int sub = W == 1 ? 0 : wid;  // this wavefront's share of the row
+    const int64_t row = (int64_t)blockIdx.x * RW + (W == 1 ? wid : 0);
     if (row >= a.n_rows) return;
     const size_t off = (size_t)row * a.ld * ES;
     const u32x4 *src = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.student) + off);
@@ -133,6 +132,16 @@ __global__ __launch_bounds__(kGradWaves *kWave) void opd_grad_kernel(GradArgs a)
         }
         return;
     }
+    constexpr int U = 4;
+    constexpr int64_t kStep = (int64_t)U * kWave;
+    const int64_t nfull = nvec / kStep;  // whole U-load chunks
+    u32x4 v[U];
+    auto load = [&](int64_t c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(src + c * kStep + u * kWave + lane);
+    };
+    if (sub < nfull) load(sub);
+    __builtin_amdgcn_sched_barrier(0);
     // log-normaliser from the scoring pass: LSE_S = s_y - log pi_S(y)
     float sy = 0.0f;
     if (ok) {
@@ -175,19 +184,13 @@ __global__ __launch_bounds__(kGradWaves *kWave) void opd_grad_kernel(GradArgs a)
         }
         return o;
     };
-    constexpr int U = 4;
-    constexpr int64_t kStep = (int64_t)U * kWave;
-    const int64_t nfull = nvec / kStep;  // whole U-load chunks
     for (int64_t c = sub; c < nfull; c += W) {
-        const int64_t k = c * kStep;
-        u32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(src + k + u * kWave + lane);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t vi = k + u * kWave + lane;
+            const int64_t vi = c * kStep + u * kWave + lane;
             __builtin_nontemporal_store(grad_vec(v[u], vi), dst + vi);
         }
+        if (c + W < nfull) load(c + W);
     }
     for (int64_t k = nfull * kStep + (int64_t)sub * kWave; k < nvec; k += (int64_t)W * kWave) {
         const int64_t vi = k + lane;
@@ -203,6 +206,30 @@ __global__ __launch_bounds__(kGradWaves *kWave) void opd_grad_kernel(GradArgs a)
                 reinterpret_cast<float *>(dst + nvec)[j] = __uint_as_float(g[j]);
         }
     }
+}
+
+template <int DT, int W, int RW>
+hipError_t launch_grad_form(const GradArgs &a, hipStream_t stream) {
+    hipLaunchKernelGGL((opd_grad_kernel<DT, W, RW>), dim3((unsigned)((a.n_rows + RW - 1) / RW)),
+                       dim3(W * RW * kWave), 0, stream, a);
+    return hipGetLastError();
+}
+
+// Wavefronts by the row's 16-byte words: as many as have words for their loads, so that fewer rows
+// are read and written at a time.  Whole call (bits equal), eight wavefronts for every length ->
+// the form taken here:
+//   words 18,992 (bf16): 64 rows 26.6 -> 21.4 us, 2,000 rows 217 -> 199, 14,000 rows, two thirds of
+//                        them retained, 1,394 -> 1,355, all retained 1,649 -> 1,610
+//   words 25,000 (fp32), 3,000 rows: 448 -> 421 us; words 4,000, 20,000 rows: 391 -> 375
+//   words 500, 20,000 rows: 70.8 -> 53.8 us; words 125, 30,000 rows: 64.1 -> 27.4
+// Sixteen take 198 us against eight's 189 at 2,000 words, eight 105 against four's 95 at 1,000.
+template <int DT>
+hipError_t launch_form(const GradArgs &a, hipStream_t stream) {
+    const int words = a.vocab / (DT == STRIDE_BF16 ? 8 : 4);
+    if (words < 256) return launch_grad_form<DT, 1, 8>(a, stream);
+    if (words < 1536) return launch_grad_form<DT, 4, 1>(a, stream);
+    if (words < 3072) return launch_grad_form<DT, 8, 1>(a, stream);
+    return launch_grad_form<DT, 16, 1>(a, stream);
 }
 
 }  // namespace
@@ -231,12 +258,8 @@ hipError_t launch_opd_grad(const stride_layout &L, int32_t unit, int32_t dtype, 
     a.ld = ld;
     a.vocab = vocab;
     a.scale = scale;
-    const unsigned rows = (unsigned)L.n_tokens;  // one workgroup per row
-    if (dtype == STRIDE_BF16)
-        hipLaunchKernelGGL(opd_grad_kernel<STRIDE_BF16>, dim3(rows), dim3(kGradWaves * kWave), 0, stream, a);
-    else
-        hipLaunchKernelGGL(opd_grad_kernel<STRIDE_F32>, dim3(rows), dim3(kGradWaves * kWave), 0, stream, a);
-    return hipGetLastError();
+    if (dtype == STRIDE_BF16) return launch_form<STRIDE_BF16>(a, stream);
+    return launch_form<STRIDE_F32>(a, stream);
 }
 
 }  // namespace stride

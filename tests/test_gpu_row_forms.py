@@ -113,3 +113,42 @@ def test_many_rows(dtype):
     for words in MANY:
         print("words", words, flush=True)
         _check(words, 16384 + 5, torch.bfloat16 if dtype == "bf16" else torch.float32, 1)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_grad_forms(dtype):
+    """The OPD gradient at the borders of its forms: retained rows against float64, the others zero,
+    padding columns and rows past the last untouched."""
+    import torch
+    import paper_2609_14636_amd as P
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    per = 8 if dtype == "bf16" else 4
+    for words in (1, 63, 255, 256, 257, 1024, 1535, 1536, 2047, 3071, 3072, 4095, 4097, 9000):
+        for pad in (0, 3):
+            vocab, n = words * per + pad, 27
+            print("words", words, "pad", pad, flush=True)
+            ld = vocab + (-vocab) % per
+            g = torch.Generator(device="cuda").manual_seed(words)
+            s = torch.empty((n, ld), dtype=td, device="cuda").normal_(0, 3, generator=g)
+            ids = torch.randint(0, vocab, (n,), dtype=torch.int32, device="cuda", generator=g)
+            ids[0], ids[1] = vocab - 1, 0
+            lay = P.Layout(torch.tensor([0, 1, 2], dtype=torch.int32, device="cuda"),
+                           torch.tensor([0, 11, n], dtype=torch.int64, device="cuda"), n)
+            path = P.Path(lay, P.STRIDE_UNIT_TOKEN)
+            path.score(vocab, [s], s, ids)
+            path.logp_t.add_(torch.linspace(-1, 1, n, device="cuda"))
+            path.stop_unit.copy_(torch.tensor([6, -1], dtype=torch.int32))
+            start = torch.tensor([2, 5], dtype=torch.int32, device="cuda")
+            buf = torch.full((n + 1, ld), 7.0, dtype=td, device="cuda")
+            path.grad(vocab, s, ids, buf[:n], None, start, scale=0.5)
+            assert int(path.flags.item()) == 0
+            keep = torch.zeros(n, dtype=torch.bool, device="cuda")
+            keep[2:7] = keep[16:] = True
+            c = 0.5 * (path.logp_t - path.logp_s).double().unsqueeze(1)
+            want = c * s[:, :vocab].double().softmax(1)
+            want[torch.arange(n, device="cuda"), ids.long()] -= c.squeeze(1)
+            got = buf[:n, :vocab].double()
+            assert (got[~keep] == 0).all() and (buf[n] == 7.0).all() and (buf[:, vocab:] == 7.0).all()
+            # one rounding to the logits' type, and fp32's exp2 argument of a logit below 32
+            tol = (2.0 ** -8 if dtype == "bf16" else 4e-6) * want[keep].abs() + 4e-6 * c[keep].abs()
+            assert ((got[keep] - want[keep]).abs() <= tol).all()
