@@ -165,8 +165,18 @@ __device__ __forceinline__ void tile_of(const FusedArgs &a, int b, int &tm, int 
     tn = (s / h) * 8 + xcd;
 }
 
-template <bool kAlone>
+// Fold one partial (max p.x, sum p.y of exp(z - p.x)) into a running (m, s).
+__device__ __forceinline__ void fold_partial(float &m, float &s, const float2 p) {
+    const float mn = fmaxf(m, p.x);
+    const float ref = (mn == -INFINITY) ? 0.0f : mn;
+    s = s * ex2((m - ref) * kLog2e) + p.y * ex2((p.x - ref) * kLog2e);
+    m = mn;
+}
+
+// NB: 16-row vocabulary blocks per wave; the tile holds 32 NB vocabulary entries.
+template <bool kAlone, int NB>
 __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
+    constexpr int kBN = 32 * NB, kWaveV = 16 * NB;  // vocabulary entries of the tile and of a wave
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     // wave-uniform values in scalar registers: the LDS-DMA destinations are scalar arithmetic
@@ -232,15 +242,15 @@ __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
         const int f = fr * kRowB + (((4 * hf + kg) ^ swz(fr)) * 16);
 #pragma unroll
         for (int g = 0; g < 3; ++g) {
-            wb[g][hf] = g * 2 * kBufB + (wv * 128) * kRowB + f;
+            wb[g][hf] = g * 2 * kBufB + (wv * kWaveV) * kRowB + f;
             hb[g][hf] = g * 2 * kBufB + (wt * 64) * kRowB + f;
             // opaque to the compiler: it would otherwise fold the pair's 64 KB step into the
             // reads' offsets, overflow their 16-bit immediate and keep a register per read
             asm volatile("" : "+v"(wb[g][hf]), "+v"(hb[g][hf]));
         }
     }
-    bf16x8 FA[8], FB[4];
-    f32x4 acc[8][4];  // the first K step's MFMAs start from zero, so no vector moves clear it
+    bf16x8 FA[NB], FB[4];
+    f32x4 acc[NB][4];  // the first K step's MFMAs start from zero, so no vector moves clear it
 
     // One 32-wide K step of this wave (half hf of stage j, whose H and W operands sit in
     // buffers hbuf and wbuf): fragments from LDS and one operand's loads, then the MFMAs.
@@ -256,7 +266,7 @@ __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
     // whose MFMAs take zero as their accumulator input.
     auto phase = [&](int j, int hf, int hbuf, int wbuf, bool may_start) __attribute__((always_inline)) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t)
+        for (int t = 0; t < NB; ++t)
             FA[t] = *reinterpret_cast<const bf16x8 *>(lds + wb[wbuf >> 1][hf] + (wbuf & 1) * kBufB +
                                                       t * 16 * kRowB);
 #pragma unroll
@@ -280,13 +290,13 @@ __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
         if (may_start && j == 0) {
             const f32x4 zero = {};
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj)
                     acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(FA[i], FB[jj], zero, 0, 0, 0);
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj)
                     acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(FA[i], FB[jj], acc[i][jj], 0, 0, 0);
@@ -325,32 +335,33 @@ __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
     if (j + 3 < ns) stage(j + 3, 3);
     if (grp == 0) barrier();  // both groups meet the same number of barriers
 
-    // ---- epilogue: per token of this wave, (max, sum exp(z - max)) over its 128 entries;
+    // ---- epilogue: per token of this wave, (max, sum exp(z - max)) over its kWaveV entries;
     // lane l holds entries i*16 + 4*(l/16) + e of token jj*16 + l%16, and the lanes l, l^16,
     // l^32, l^48 that share a token combine theirs with two exchanges ----
     const int q4 = lane >> 4;
-    const int64_t v_base = n0 + wv * 128;
-    const int vlim = (int)((a.vocab - v_base) < 128 ? (a.vocab - v_base) : 128);  // valid entries
+    const int64_t v_base = n0 + wv * kWaveV;
+    const int vlim = (int)((a.vocab - v_base) < kWaveV ? (a.vocab - v_base) : kWaveV);  // valid entries
     const int hidx = tn * 2 + wv;
+    float2 both[4];
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
-        if (vlim < 128) {
+        if (vlim < kWaveV) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (i * 16 + q4 * 4 + e >= vlim) acc[i][jj][e] = -INFINITY;
         }
         float m = acc[0][jj][0];
 #pragma unroll
-        for (int x = 1; x < 32; ++x) m = fmaxf(m, acc[x >> 2][jj][x & 3]);
+        for (int x = 1; x < 4 * NB; ++x) m = fmaxf(m, acc[x >> 2][jj][x & 3]);
         m = fmaxf(m, __shfl_xor(m, 16, 64));
         m = fmaxf(m, __shfl_xor(m, 32, 64));
         const float ref = (m == -INFINITY) ? 0.0f : m;
         const float mref = ref * kLog2e;
         float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
-        for (int x = 0; x < 32; x += 2) {
+        for (int x = 0; x < 4 * NB; x += 2) {
             s0 += ex2(__builtin_fmaf(acc[x >> 2][jj][x & 3], kLog2e, -mref));
             s1 += ex2(__builtin_fmaf(acc[(x + 1) >> 2][jj][(x + 1) & 3], kLog2e, -mref));
         }
@@ -358,21 +369,36 @@ __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
         sum += __shfl_xor(sum, 16, 64);
         sum += __shfl_xor(sum, 32, 64);
         const int64_t row = m0 + wt * 64 + jj * 16 + (lane & 15);
-        if (q4 == 0 && hidx < a.n_half && row < a.n_rows)
+        if (kAlone) {
+            both[jj] = make_float2(m, sum);
+        } else if (q4 == 0 && hidx < a.n_half && row < a.n_rows) {
             a.partial[(int64_t)hidx * a.n_rows + row] = make_float2(m, sum);
+        }
+    }
+    if (kAlone) {  // one partial per tile: the second vocabulary half's through LDS
+        float2 *half = reinterpret_cast<float2 *>(lds);
+        __syncthreads();  // every wave is done with the ring
+        if (wv == 1 && q4 == 0) {
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) half[wt * 64 + jj * 16 + (lane & 15)] = both[jj];
+        }
+        __syncthreads();
+        if (wv == 0 && q4 == 0) {
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const int i = wt * 64 + jj * 16 + (lane & 15);
+                fold_partial(both[jj].x, both[jj].y, half[i]);
+                if (m0 + i < a.n_rows) a.partial[(int64_t)tn * a.n_rows + m0 + i] = both[jj];
+            }
+        }
     }
 }
 
-__global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) { fused_lse<false>(a); }
-__global__ __launch_bounds__(kThreads, 1) void fused_lse_alone_kernel(FusedArgs a) { fused_lse<true>(a); }
-
-// Fold one partial (max p.x, sum p.y of exp(z - p.x)) into a running (m, s).
-__device__ __forceinline__ void fold_partial(float &m, float &s, const float2 p) {
-    const float mn = fmaxf(m, p.x);
-    const float ref = (mn == -INFINITY) ? 0.0f : mn;
-    s = s * ex2((m - ref) * kLog2e) + p.y * ex2((p.x - ref) * kLog2e);
-    m = mn;
-}
+__global__ __launch_bounds__(kThreads, 1) void fused_lse_kernel(FusedArgs a) { fused_lse<false, 8>(a); }
+__global__ __launch_bounds__(kThreads, 1) void fused_row8_kernel(FusedArgs a) { fused_lse<true, 8>(a); }
+__global__ __launch_bounds__(kThreads, 1) void fused_row7_kernel(FusedArgs a) { fused_lse<true, 7>(a); }
+__global__ __launch_bounds__(kThreads, 1) void fused_row6_kernel(FusedArgs a) { fused_lse<true, 6>(a); }
+__global__ __launch_bounds__(kThreads, 1) void fused_row4_kernel(FusedArgs a) { fused_lse<true, 4>(a); }
 
 // ---- up to 128 rows ----
 // The same product where reading W once bounds it (N <= 128): one workgroup per
@@ -680,7 +706,10 @@ hipError_t ensure_lds_limit() {
     const uint64_t bit = (dev >= 0 && dev < 64) ? (1ull << dev) : 0;
     if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
     for (const void *f : {reinterpret_cast<const void *>(fused_lse_kernel),
-                          reinterpret_cast<const void *>(fused_lse_alone_kernel),
+                          reinterpret_cast<const void *>(fused_row8_kernel),
+                          reinterpret_cast<const void *>(fused_row7_kernel),
+                          reinterpret_cast<const void *>(fused_row6_kernel),
+                          reinterpret_cast<const void *>(fused_row4_kernel),
                           reinterpret_cast<const void *>(fused_rows64_kernel),
                           reinterpret_cast<const void *>(fused_rows128_kernel)}) {
         e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
@@ -755,13 +784,38 @@ hipError_t launch_fused_teacher(const uint16_t *h, const uint16_t *w, const int3
             return launch_merge(a, ids, logp_t, flags, stream);
         }
     }
+    if (a.tiles_m == 1) {
+        // One row tile: of the tile heights built (32 n entries), the one that takes least.  A round
+        // of tiles over the 256 CUs took time like n + 6 (d = 2,048; three rounds of n = 8 154 us, three
+        // of 7 143, four of 6 168, five of 4 186).  Measured, n = 8 -> the one chosen: 218 rows,
+        // V = 151,936 172 -> 161 us (n = 7); 200 rows, V = 81,000 104 -> 89 (6), 50,000 56 -> 53 (7),
+        // d = 4,096, V = 20,000 81 -> 62 (4).
+        int nb = 8;
+        int64_t least = INT64_MAX;
+        for (const int n : {8, 7, 6, 4}) {
+            const int64_t tiles = ((int64_t)vocab + 32 * n - 1) / (32 * n);
+            const int64_t cost = (tiles + kCUs - 1) / kCUs * (n + 6);
+            if (cost < least) {
+                least = cost;
+                nb = n;
+            }
+        }
+        a.tiles_n = (vocab + 32 * nb - 1) / (32 * nb);
+        a.super_cols = a.tiles_n / 16;
+        a.n_half = a.tiles_n;  // one partial per tile, at most one per 128 entries
+        hipLaunchKernelGGL(nb == 8 ? fused_row8_kernel : (nb == 7 ? fused_row7_kernel
+                                                                 : (nb == 6 ? fused_row6_kernel : fused_row4_kernel)),
+                           dim3((unsigned)(8 * ((a.tiles_n + 7) / 8))), dim3(kThreads), kLdsBytes, stream, a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return launch_merge(a, ids, logp_t, flags, stream);
+    }
     const int64_t rem = a.tiles_m - a.super_rows * 16;
     const int64_t blocks = 8 * ((int64_t)a.super_rows * a.super_cols * 32 +
                                 (int64_t)a.super_rows * 2 * (a.tiles_n - a.super_cols * 16) +
                                 rem * ((a.tiles_n + 7) / 8));
     if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;  // grid past the 32-bit limit
-    hipLaunchKernelGGL(a.tiles_m == 1 ? fused_lse_alone_kernel : fused_lse_kernel, dim3((unsigned)blocks),
-                       dim3(kThreads), kLdsBytes, stream, a);
+    hipLaunchKernelGGL(fused_lse_kernel, dim3((unsigned)blocks), dim3(kThreads), kLdsBytes, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_merge(a, ids, logp_t, flags, stream);

@@ -100,6 +100,9 @@ def test_fused_tile_numbering(rows, vocab):
     (40, 140000, 576),  # 4,375 blocks: three passes of six; nine stages
     (129, 33000, 256),  # one tile row past the form: each tile starts at its own stage
     (256, 5000, 448),
+    (200, 33000, 64),   # tiles of 192 entries, one K stage
+    (200, 50001, 128),  # tiles of 224, the last of one entry in its second half's rows
+    (190, 65536, 64),   # tiles of 256, one per CU
 ])
 def test_fused_few_rows(rows, vocab, d):
     """Up to 128 rows W streams through registers in equal shares, and up to 256 a tile row starts
