@@ -795,7 +795,7 @@ def main():
     achieved = bytes_alg / (score_ms * 1e-3) / 1e9
     traffic = None if args.exact_kl else measured_traffic(args.workload)
     dt = "bf16" if wl.dtype == W.BF16 else "f32"
-    # streaming-read reference: the same rows read with the same access pattern, no arithmetic
+    # streaming-read reference: the same rows, one wavefront per row, the same loads, no arithmetic
     sink = torch.empty(2 * n_tok, dtype=torch.int32, device="cuda")
     read_bytes = (wl.vocab * wl.esize) // 16 * 16
     pev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))

@@ -117,7 +117,7 @@ size_t stride_workspace_size(const stride_layout *layout, int32_t unit);
  *                    vocabulary, KL(pi_S || pi_T) = sum_v pi_S(v) log(pi_S(v) / pi_T(v)),
  *                    the divergence whose sequence-level form OPD minimises (Sec. 3.1);
  *                    needs student_logits.  Computed in the same single pass over both
- *                    rows (one wavefront reads the token's teacher and student rows).
+ *                    rows.
  *   turn_mean        [T] double output
  *   dev_flags        device uint32 or NULL
  *
@@ -305,10 +305,9 @@ stride_status stride_records_plan(stride_records *rec, int32_t n_tasks, const in
 /* Streaming-read reference (a measurement aid, not a step of the method).
  *
  * Reads n_rows rows of `a` (and, when b is not NULL, the same rows of `b`,
- * interleaved row by row) with the scoring kernel's access pattern for batches of
- * 16,384 row items or more -- one wavefront per row, 16-byte non-temporal loads
- * -- and does no arithmetic, so
- * timing it gives the read bandwidth that pattern reaches; the scoring kernel's
+ * interleaved row by row) with one wavefront per row and 16-byte non-temporal loads, as the
+ * scoring kernel reads them (which gives long rows up to sixteen wavefronts), and does no
+ * arithmetic, so timing it gives the read bandwidth that pattern reaches; the scoring kernel's
  * bandwidth is reported as a fraction of it next to the fraction of peak.
  *   a, b        device rows, 16-byte aligned; b may be NULL
  *   n_rows      rows to read from each matrix (>= 0)
@@ -336,8 +335,8 @@ stride_status stride_probe_read_flat(const void *a, const void *b, int64_t n_byt
                                      int64_t sink_len, hipStream_t stream);
 
 /* Streaming read+write reference for the OPD gradient's roofline (a measurement aid,
- * not a step of the method): moves n_rows rows as stride_opd_grad does -- eight
- * wavefronts per row, a 16-byte non-temporal load and store per word -- copying the
+ * not a step of the method): moves n_rows rows as stride_opd_grad does, with eight
+ * wavefronts per row (the gradient has up to sixteen for long rows) -- a 16-byte non-temporal load and store per word -- copying the
  * first copy_bytes of each row of src to dst; a row whose row_mask byte is 0 is
  * written as zeros without being read (row_mask may be NULL: every row copied).
  *   src, dst    device rows of row_bytes (a multiple of 16), 16-byte aligned

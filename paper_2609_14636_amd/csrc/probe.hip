@@ -1,15 +1,15 @@
 // probe.hip -- streaming references for the rooflines of the row kernels.
 //
-// Not part of the method.  probe_read_kernel reads rows exactly as the scoring
-// kernel does (one wavefront per row, 16-byte non-temporal loads with eight per
-// lane in flight, rows of the two matrices interleaved item by item) and does no
+// Not part of the method.  probe_read_kernel reads rows with the scoring kernel's
+// loads (16-byte non-temporal, eight per lane in flight, rows of the two matrices
+// interleaved item by item), one wavefront per row at any size, and does no
 // arithmetic beyond an XOR, so its rate is the read bandwidth this access pattern
 // reaches on the device; the scoring kernel's bandwidth divided by this rate says
 // how much of the reachable bandwidth the softmax arithmetic leaves on the table.
 // probe_flat_kernel reads the same bytes as one contiguous range per matrix in a
 // grid-stride order (the plainest streaming order), to tell the access pattern
-// apart from the footprint.  probe_copy_kernel moves rows as the OPD gradient
-// kernel does: eight wavefronts per row (wavefront w takes the row's 4-load chunks
+// apart from the footprint.  probe_copy_kernel moves rows with the OPD gradient
+// kernel's loads and stores: eight wavefronts per row (wavefront w takes the row's 4-load chunks
 // w, w + 8, ...), a 16-byte non-temporal load and store per word; rows whose mask
 // byte is 0 are written as zeros without being read.
 #include "common.hpp"

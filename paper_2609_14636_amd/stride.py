@@ -302,7 +302,7 @@ def stride_opd_grad(layout: Layout, unit: int, vocab: int, student_logits: torch
 def stride_probe_read(a: torch.Tensor, b: torch.Tensor | None, read_bytes: int,
                       sink: torch.Tensor, stream=None) -> None:
     """Streaming-read reference: reads the first read_bytes of every row of a (and b) with the
-    scoring kernel's access pattern and no arithmetic (a measurement aid)."""
+    scoring kernel's loads, one wavefront per row, and no arithmetic (a measurement aid)."""
     if b is not None and (b.stride() != a.stride() or b.shape != a.shape or b.dtype != a.dtype):
         raise ValueError("a and b must share shape, dtype and strides")
     _check(_lib.stride_probe_read(_ptr(a), _ptr(b), a.shape[0], a.stride(0) * a.element_size(),
