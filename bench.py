@@ -373,7 +373,7 @@ def bench_fused(args):
                      "unit": "TFLOP/s", "frac": achieved / MFMA_BF16_PEAK_TFLOPS,
                      "traffic": measured_traffic("fused", FUSED_SRC, "fused_hip_sha256_16"),
                      "kernel": "fused_lse_kernel (bf16 MFMA 16x16x32); kernel_ms brackets the "
-                               "teacher call (projection + per-row gather + merge)",
+                               "teacher call (projection + merge with the per-row dot product)",
                      "kernel_ms": k_ms, "kernel_ms_median": k_stats["median"],
                      "kernel_ms_min": k_stats["min"],
                      "mfma_busy": measured_mfma_busy(),

@@ -336,7 +336,8 @@ stride_status stride_probe_read_flat(const void *a, const void *b, int64_t n_byt
 
 /* Streaming read+write reference for the OPD gradient's roofline (a measurement aid,
  * not a step of the method): moves n_rows rows as stride_opd_grad does, with eight
- * wavefronts per row (the gradient has up to sixteen for long rows) -- a 16-byte non-temporal load and store per word -- copying the
+ * wavefronts per row (the gradient has up to sixteen for long rows) and a 16-byte non-temporal
+ * load and store per word, copying the
  * first copy_bytes of each row of src to dst; a row whose row_mask byte is 0 is
  * written as zeros without being read (row_mask may be NULL: every row copied).
  *   src, dst    device rows of row_bytes (a multiple of 16), 16-byte aligned
