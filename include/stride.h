@@ -350,7 +350,7 @@ stride_status stride_probe_copy(const void *src, void *dst, const uint8_t *row_m
  *
  * In the library built for testing (libstride_debug.so, scan compiled with
  * STRIDE_SCAN_DELAY_HOOK), later stride_stop / stride_stop_noalloc calls that scan tiles (more
- * than 2^19 units, or 2^15 per rollout on average) make those
+ * than 2^19 units, 2^15 per rollout on average or 2^15 rollouts) make those
  * picked by a hash of (seed, tile) -- about one in `one_in` -- sleep 1 .. `sleeps` times
  * s_sleep(127) (about 8,000 cycles each) before publishing their aggregate, so that their
  * successors look back over descriptors that are not yet published.  The waits stay far below

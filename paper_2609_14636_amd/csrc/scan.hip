@@ -35,15 +35,18 @@ namespace stride {
 namespace {
 
 constexpr int kSlots = 256;            // rollouts per tile held in LDS
-// Units of the call, and of its average rollout, up to which each rollout gets a group of threads
+// Units of the call and of its average rollout, and rollouts, up to which each gets a group of threads
 // of its own (stop_rollout_kernel, one launch) instead of the tiles' three launches.  The whole
 // test, tiles -> groups: 8 x 8 units 17.7 -> 3.6 us, 2,000 x 12 24.2 -> 4.7, 64 x 4,096 25.6 ->
 // 7.3, 2 x 30,000 23.4 -> 15.9.  A group scans its rollout alone, about 3 us for every 8,192
 // units, where tiles spread it over the chip: one rollout of 172,000 units takes 61.6 us as a
 // group and 20.4 as tiles, one of 516,000 196 and 29.5.  The host does not know the longest
-// rollout, so the call's own limit bounds what one long rollout among short ones can cost.
+// rollout, so the call's own limit bounds what one long rollout among short ones can cost.  Short
+// rollouts cost a workgroup for every four: 32,768 of 8 units take 14.6 us against the tiles' 31.9,
+// 100,000 of 3 36.1 against 32.9, 200,000 of 2 77 against 35.7.
 constexpr int64_t kRolloutUnits = 1 << 19;
 constexpr int64_t kRolloutLength = 1 << 15;
+constexpr int64_t kRolloutCount = 1 << 15;
 constexpr uint32_t kSpinLimit = 1u << 22;
 
 struct StopArgs {
@@ -681,7 +684,8 @@ hipError_t launch_stop(const stride_layout &L, int32_t unit, const void *values,
 #endif
 
     const int64_t per = L.n_rollouts > 0 ? n_units / L.n_rollouts : 0;
-    if (L.n_rollouts > 0 && n_units <= kRolloutUnits && per <= kRolloutLength) {
+    if (L.n_rollouts > 0 && L.n_rollouts <= kRolloutCount && n_units <= kRolloutUnits &&
+        per <= kRolloutLength) {
         if (unit == STRIDE_UNIT_TURN)
             return launch_stop_rollouts<double>(a, per, stream);
         return launch_stop_rollouts<float>(a, per, stream);

@@ -84,3 +84,26 @@ def test_units_in_no_rollout():
     c = cum.cpu().numpy()
     assert np.isnan(c[:3]).all() and np.isnan(c[9:12]).all() and (c[12:] == 5.0).all()
     assert c[3:9].tolist() == [-1, -2, -1, -2, -3, -4] and stop.tolist() == [-1, 2]
+
+
+def test_many_short_rollouts_as_tiles():
+    """One rollout more than the groups take: the tile scan, against float64 sums."""
+    import torch
+    import paper_2609_14636_amd as P
+    R = (1 << 15) + 1
+    g = np.random.default_rng(4)
+    off = np.concatenate([[0], np.cumsum(g.integers(0, 5, R))]).astype(np.int64)
+    U = int(off[-1])
+    vals = -np.abs(g.normal(0.5, 0.5, U))
+    lam = [-1.2]
+    cum_o, stop_o, ret_o = H.OP.O.stop(off, vals, np.full(R, lam[0]), np.zeros(R, np.int32),
+                                       np.arange(U + 1, dtype=np.int64))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    lay = P.Layout(dev(off.astype(np.int32)), dev(np.arange(U + 1, dtype=np.int64)), U)
+    path = P.Path(lay, P.STRIDE_UNIT_TURN, with_student=False)
+    P.stride_stop(lay, P.STRIDE_UNIT_TURN, dev(vals), lam, None, path.cum, path.stop_unit, path.retained,
+                  path.flags, path.ws)
+    assert int(path.flags.item()) == 0
+    assert np.max(np.abs(path.cum.cpu().numpy() - cum_o)) <= 1e-12
+    assert np.array_equal(path.stop_unit.cpu().numpy(), stop_o)
+    assert np.array_equal(path.retained.cpu().numpy(), ret_o)
