@@ -199,16 +199,21 @@ __global__ __launch_bounds__(W *RW *kWave) void score_rows_kernel(ScoreArgs a) {
         for (int u = 0; u < U; ++u) unpack<DT>(v[u], x + u * E);
         fold<U * E>(m, s0, s1, x);
     };
-    // words after the last whole chunk, every W-th block of 64 of them; -inf past the row
+    // words after the last whole chunk, every W-th block of 64 of them; -inf past the row.  Fetched
+    // first, unless they are so many that holding them through the row costs occupancy.
     constexpr int kRest = (U + W - 1) / W;
+    constexpr bool kRestFirst = kRest <= 4;
     u32x4 rest[kRest];
+    auto load_rest = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < kRest; ++i) {
-        const int k = nfull * kStep + (i * W + wave) * kWave + lane;
-        constexpr uint32_t n = Elem<DT>::kNegInf;
-        rest[i] = u32x4{n, n, n, n};
-        if (k < nvec) rest[i] = __builtin_nontemporal_load(p + k);
-    }
+        for (int i = 0; i < kRest; ++i) {
+            const int k = nfull * kStep + (i * W + wave) * kWave + lane;
+            constexpr uint32_t n = Elem<DT>::kNegInf;
+            rest[i] = u32x4{n, n, n, n};
+            if (k < nvec) rest[i] = __builtin_nontemporal_load(p + k);
+        }
+    };
+    if (kRestFirst) load_rest();
     u32x4 v[D][U];
     if (D == 1) {
         for (int i = 0; i < mine; ++i) {
@@ -234,6 +239,7 @@ __global__ __launch_bounds__(W *RW *kWave) void score_rows_kernel(ScoreArgs a) {
             if (i + d < mine) use(v[d % D]);
         }
     }
+    if (!kRestFirst) load_rest();
 #pragma unroll
     for (int i = 0; i < kRest; ++i) {
         float x[E];
@@ -581,14 +587,19 @@ hipError_t launch_rows_form(const ScoreArgs &a, hipStream_t stream) {
 // Sixteen wavefronts pay at two or three of their rounds of 8,192 words: 1,201 against 1,211 us
 // at 16,384 words, 1% slower than eight at 25,000.  fp32 rows hold half the arithmetic per word and
 // leave registers for two such workgroups per CU: sixteen from 8,192 words on (853 against 869 us
-// at 12,500 words, 30,000 rows).
+// at 12,500 words, 30,000 rows).  From 196,608 rows of those lengths on one wavefront per row keeps up
+// on a warm card (262,144 rows 11,904 us against 11,696) and is ahead on a cool one (11,398 against
+// 11,614), so it stays there.
 template <int DT>
 hipError_t launch_rows(const ScoreArgs &a, hipStream_t stream) {
     const int words = a.vocab / Elem<DT>::kPerVec;
-    const bool many = (a.student ? 2 * a.n_rows : a.n_rows) >= 16384;
+    const int64_t items = a.student ? 2 * a.n_rows : a.n_rows;
+    const bool many = items >= 16384;
     if (words < 1024) return launch_rows_form<DT, 1, 8, 4, 1>(a, stream);
     if (words < 3072) return launch_rows_form<DT, 4, 1, 8, 1>(a, stream);
     if (words < 8192) return launch_rows_form<DT, 8, 1, 8, 1>(a, stream);
+    if (DT == STRIDE_BF16 && items >= 196608 && words >= 16384 && words < 24576)
+        return launch_rows_form<STRIDE_BF16, 1, 8, 8, 1>(a, stream);
     if (many && (DT == STRIDE_F32 || (words >= 16384 && words < 24576)))
         return launch_rows_form<DT, 16, 1, 8, 1>(a, stream);
     return launch_rows_form<DT, 8, 1, 4, 3>(a, stream);
