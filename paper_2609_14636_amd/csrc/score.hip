@@ -22,6 +22,11 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.69314718055994531f;
 constexpr uint8_t kBadDomain = 0xFF;
+// Lowest reference point of a (max, sum) state: times log2(e) it is still finite in fp32.  A state that
+// has seen only values below it (-inf, or a mask of the type's lowest value) has sum 0 and leaves no
+// trace in the states that it is merged with; with the maximum itself as reference its sum would be
+// infinite, and NaN after the merge.
+constexpr float kLowestRef = -2.358e38f;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int DT>
@@ -60,15 +65,14 @@ __device__ __forceinline__ void unpack<STRIDE_F32>(const u32x4 &v, float *x) {
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Fold n values into the lane's running (m, s0 + s1).  The reference point is
-// the running maximum; a state that has only seen -inf keeps reference 0 so
-// that -inf - -inf never appears.
+// the running maximum, at least kLowestRef, so that -inf - -inf never appears.
 template <int N>
 __device__ __forceinline__ void fold(float &m, float &s0, float &s1, const float *x) {
     float cm = x[0];
 #pragma unroll
     for (int i = 1; i < N; ++i) cm = fmaxf(cm, x[i]);
     const float mn = fmaxf(m, cm);
-    const float ref = (mn == -INFINITY) ? 0.0f : mn;
+    const float ref = fmaxf(mn, kLowestRef);
     const float scale = fast_exp2((m - ref) * kLog2e);
     s0 *= scale;
     s1 *= scale;
@@ -84,7 +88,7 @@ __device__ __forceinline__ void fold(float &m, float &s0, float &s1, const float
 // Merge two (m, s) states.
 __device__ __forceinline__ void merge(float &m, float &s, float m2, float s2) {
     const float mn = fmaxf(m, m2);
-    const float ref = (mn == -INFINITY) ? 0.0f : mn;
+    const float ref = fmaxf(mn, kLowestRef);
     s = s * fast_exp2((m - ref) * kLog2e) + s2 * fast_exp2((m2 - ref) * kLog2e);
     m = mn;
 }
@@ -291,8 +295,8 @@ __device__ __forceinline__ void fold_pair(float &mt, float &zt, float &ms, float
         cs = fmaxf(cs, x[i]);
     }
     const float mtn = fmaxf(mt, ct), msn = fmaxf(ms, cs);
-    const float rt = (mtn == -INFINITY) ? 0.0f : mtn;
-    const float rs = (msn == -INFINITY) ? 0.0f : msn;
+    const float rt = fmaxf(mtn, kLowestRef);
+    const float rs = fmaxf(msn, kLowestRef);
     zt *= fast_exp2((mt - rt) * kLog2e);
     const float ss = fast_exp2((ms - rs) * kLog2e);
     zs *= ss;
@@ -331,7 +335,7 @@ __device__ __forceinline__ void pair_merge(float &mt, float &zt, float &ms, floa
                                            float mt2, float zt2, float ms2, float zs2, float am2) {
     merge(mt, zt, mt2, zt2);
     const float mn = fmaxf(ms, ms2);
-    const float ref = (mn == -INFINITY) ? 0.0f : mn;
+    const float ref = fmaxf(mn, kLowestRef);
     const float f1 = fast_exp2((ms - ref) * kLog2e), f2 = fast_exp2((ms2 - ref) * kLog2e);
     zs = zs * f1 + zs2 * f2;
     am = am * f1 + am2 * f2;

@@ -152,3 +152,46 @@ def test_grad_forms(dtype):
             # one rounding to the logits' type, and fp32's exp2 argument of a logit below 32
             tol = (2.0 ** -8 if dtype == "bf16" else 4e-6) * want[keep].abs() + 4e-6 * c[keep].abs()
             assert ((got[keep] - want[keep]).abs() <= tol).all()
+
+
+def _masked(words, n, dtype, masked, exact_kl):
+    """Rows whose entries [masked) hold the type's lowest value: they carry no mass, so the rest of the
+    row gives the log-probability, the divergence and no flag."""
+    import torch
+    import paper_2609_14636_amd as P
+    per = 8 if dtype is torch.bfloat16 else 4
+    vocab = words * per
+    g = torch.Generator(device="cuda").manual_seed(words)
+    t, s = (torch.empty((n, vocab), dtype=dtype, device="cuda").normal_(0, 3, generator=g) for _ in range(2))
+    lo, hi = masked
+    t[:, lo * per:hi * per] = s[:, lo * per:hi * per] = torch.finfo(dtype).min
+    keep = torch.cat([torch.arange(lo * per), torch.arange(hi * per, vocab)]).cuda()
+    ids = keep[torch.randint(0, keep.numel(), (n,), device="cuda", generator=g)].int()
+    lay = P.Layout(torch.tensor([0, 1], dtype=torch.int32, device="cuda"),
+                   torch.tensor([0, n], dtype=torch.int64, device="cuda"), n)
+    path = P.Path(lay, P.STRIDE_UNIT_TURN, exact_kl=exact_kl)
+    path.score(vocab, [t], s, ids)
+    assert int(path.flags.item()) == 0
+    at = torch.arange(0, n, max(1, n // 64), device="cuda")
+    lt, ls = (x[at][:, keep].double().log_softmax(1) for x in (t, s))
+    col = torch.searchsorted(keep, ids[at].long()).unsqueeze(1)
+    # the bounds of _check and _check_pairs
+    for got, want in ((path.logp_t, lt), (path.logp_s, ls)):
+        assert float((got[at].double() - want.gather(1, col).squeeze(1)).abs().max()) <= 2e-5
+    if exact_kl:
+        want = (ls.exp() * (ls - lt)).sum(1)
+        assert float((path.kl_full[at].double() - want).abs().max()) <= 1e-4
+
+
+# words of the row, rows, masked words: whole loads of a lane, or all that a wavefront reads
+MASKED = [(1280, 16384, (1152, 1280)), (256, 16384, (0, 192)), (512, 40, (0, 256)), (8192, 40, (512, 1024)),
+          (2048, 40, (1024, 1536)), (16384, 16384, (512, 1024)), (6400, 40, (2048, 4096))]
+
+
+@pytest.mark.parametrize("exact_kl", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_masks_of_the_lowest_value(dtype, exact_kl):
+    import torch
+    for words, n, masked in MASKED:
+        print("words", words, "rows", n, "masked", masked, flush=True)
+        _masked(words, n, torch.bfloat16 if dtype == "bf16" else torch.float32, masked, exact_kl)
