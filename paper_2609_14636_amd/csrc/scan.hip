@@ -36,17 +36,24 @@ namespace {
 
 constexpr int kSlots = 256;            // rollouts per tile held in LDS
 // Units of the call and of its average rollout, and rollouts, up to which each gets a group of threads
-// of its own (stop_rollout_kernel, one launch) instead of the tiles' three launches.  The whole
-// test, tiles -> groups: 8 x 8 units 17.7 -> 3.6 us, 2,000 x 12 24.2 -> 4.7, 64 x 4,096 25.6 ->
-// 7.3, 2 x 30,000 23.4 -> 15.9.  A group scans its rollout alone, about 3 us for every 8,192
-// units, where tiles spread it over the chip: one rollout of 172,000 units takes 61.6 us as a
-// group and 20.4 as tiles, one of 516,000 196 and 29.5.  The host does not know the longest
-// rollout, so the call's own limit bounds what one long rollout among short ones can cost.  Short
-// rollouts cost a workgroup for every four: 32,768 of 8 units take 14.6 us against the tiles' 31.9,
-// 100,000 of 3 36.1 against 32.9, 200,000 of 2 77 against 35.7.
+// of its own (one launch) instead of the tiles' three launches.  The whole test, tiles -> groups:
+// 8 x 8 units 17.7 -> 3.6 us, 2,000 x 12 24.2 -> 4.7, 64 x 4,096 25.6 -> 7.3, 2 x 30,000 23.4 -> 15.9.
+// A group scans its rollout alone, where tiles spread it over the chip: one rollout of 172,000 units
+// takes 61.6 us as a group and 20.4 as tiles, one of 516,000 196 and 29.5.  The host does not know the
+// longest rollout, so the call's own limit bounds what one long rollout among short ones can cost:
+// about 0.5 us for every 1,024 units (scan_long), 285 us at 500,000.  Short rollouts cost a workgroup
+// for every four: 32,768 of 8 units take 14.9 us against the tiles' 31.9, 100,000 of 3 36.1 against
+// 32.9, 200,000 of 2 77 against 35.7.
 constexpr int64_t kRolloutUnits = 1 << 19;
 constexpr int64_t kRolloutLength = 1 << 15;
 constexpr int64_t kRolloutCount = 1 << 15;
+// Where the average rollout has at most 128 units, one wave takes each of up to kWaveLength units, eight
+// of its chunks, and kHelpers workgroups of the same launch the longer ones.  A wave walks 128 units a
+// chunk: 40,000 units before 1,500 rollouts of 3 took it 96 us, a helper 23.7 (the tiles of before 26);
+// 1,200 before 30 of 5 take 5.9 us either way.  A prime number of helpers, so that long rollouts at
+// regular places are spread over them.
+constexpr int64_t kWaveLength = 1024;
+constexpr int kHelpers = 127;
 constexpr uint32_t kSpinLimit = 1u << 22;
 
 struct StopArgs {
@@ -423,10 +430,20 @@ __device__ __forceinline__ double wave_scan(double x) {
     return x;
 }
 
+typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
+
+// The last lane's x, in scalar registers.
+__device__ __forceinline__ double last_lane(double x) {
+    const uint64_t v = (uint64_t)__double_as_longlong(x);
+    const uint32_t h = __builtin_amdgcn_readlane((uint32_t)(v >> 32), kWave - 1);
+    const uint32_t l = __builtin_amdgcn_readlane((uint32_t)v, kWave - 1);
+    return __longlong_as_double((long long)(((uint64_t)h << 32) | l));
+}
+
 // Up to N consecutive elements from p on (p + j < end), as few loads as their number allows; the
 // addresses have the element's own alignment only, which global loads of several words accept.
-template <typename VT, int N>
-__device__ __forceinline__ void load_items(const VT *vals, int64_t u, int64_t hi, VT *x) {
+template <typename VT, int N, typename I>
+__device__ __forceinline__ void load_items(const VT *vals, I u, I hi, VT *x) {
     constexpr int kPer = 16 / sizeof(VT) < N ? 16 / sizeof(VT) : N;
     typedef VT Vec __attribute__((ext_vector_type(kPer), aligned(sizeof(VT))));
     if (u + N <= hi) {
@@ -442,46 +459,82 @@ __device__ __forceinline__ void load_items(const VT *vals, int64_t u, int64_t hi
     }
 }
 
-// The whole test of one rollout by a group of NT threads, NI units each at a time: no tiles, no
-// look-back, one launch.  The units run through a fixed scan (a thread's items in order, a
-// shuffle tree, waves in order, chunks in order), so cum is bit-reproducible; the next chunk's
-// values are in flight while one is scanned.  Latency bounds it: offsets, then values, K0 and
-// domain together, then a chunk after the other.  kRolloutUnits has what it measured.
-// Groups of one wave share a workgroup of 256 threads and meet no barrier.
-template <typename VT, int NT, int NI>
-__global__ __launch_bounds__(NT < 256 ? 256 : NT) void stop_rollout_kernel(StopArgs a) {
-    static_assert(NT == kWave || NT >= 256, "a group is one wave or a whole workgroup");
-    constexpr int kGroups = NT == kWave ? 4 : 1, kWaves = NT / kWave;
-    __shared__ double s_sum[2][kWaves];
-    __shared__ int32_t s_best[kWaves];
-    const int tid = threadIdx.x % NT, lane = threadIdx.x & (kWave - 1), wave = tid / kWave;
+// A rollout as its group sees it: [lo, hi) its units inside [0, U), `from` the first one after K0.
+struct Rollout {
+    int64_t r, first, n, lo, from, hi;
+    double lam;
+};
+
+__device__ __forceinline__ Rollout rollout_of(const StopArgs &a, int64_t r, bool report) {
     const int64_t R = a.L.n_rollouts, T = a.L.n_turns, U = a.n_units;
-    const int64_t r = (int64_t)blockIdx.x * kGroups + __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
-    if (r >= R) return;
-    const VT *vals = static_cast<const VT *>(a.values);
     const int64_t t0 = a.L.rollout_turn_off[r], t1 = a.L.rollout_turn_off[r + 1];
     const int32_t start = a.start ? a.start[r] : 0, d = a.L.domain ? a.L.domain[r] : 0;
-    if (tid == 0 && (t0 < 0 || t0 > T || (r == 0 && t0 != 0) || t1 < t0 ||
-                     (r == R - 1 && t1 != T)))
+    if (report && (t0 < 0 || t0 > T || (r == 0 && t0 != 0) || t1 < t0 || (r == R - 1 && t1 != T)))
         raise_flag(a.flags, STRIDE_FLAG_BAD_OFFSETS);
     int64_t first = t0 < 0 ? 0 : (t0 > T ? T : t0), last = t1 < 0 ? 0 : (t1 > T ? T : t1);
     if (a.unit == STRIDE_UNIT_TOKEN) {
         first = a.L.turn_tok_off[first];
         last = a.L.turn_tok_off[last];
     }
-    const int64_t n = last - first;
+    Rollout o;
+    o.r = r;
+    o.first = first;
+    o.n = last - first;
     int64_t k0 = start;
-    k0 = k0 < 0 ? 0 : (k0 > n ? n : k0);
-    const double lam = (d >= 0 && d < a.n_dom) ? a.lambda.v[d] : __builtin_nan("");
+    k0 = k0 < 0 ? 0 : (k0 > o.n ? o.n : k0);
+    o.lam = (d >= 0 && d < a.n_dom) ? a.lambda.v[d] : __builtin_nan("");
     // offsets that do not cover [0, U) or leave it (flagged where they are not the caller's own
     // row offsets): units in no rollout are NaN, and no access leaves [0, U)
-    const int64_t lo = first < 0 ? 0 : first, hi = last > U ? U : last;
-    if (r == 0)
-        for (int64_t u = tid; u < first && u < U; u += NT) a.cum[u] = __builtin_nan("");
-    if (r == R - 1)
-        for (int64_t u = (last < 0 ? 0 : last) + tid; u < U; u += NT) a.cum[u] = __builtin_nan("");
-    const int64_t from = first + k0 < lo ? lo : first + k0;
-    for (int64_t u = lo + tid; u < from && u < hi; u += NT) a.cum[u] = 0.0;
+    o.lo = first < 0 ? 0 : first;
+    o.hi = last > U ? U : last;
+    o.from = first + k0 < o.lo ? o.lo : first + k0;
+    return o;
+}
+
+// NaN for the units before the first rollout's and past the last one's, 0 for those before K0; tid and
+// NT: the number and count of the threads that share the rollout.
+__device__ __forceinline__ void fill_outside(const StopArgs &a, const Rollout &o, int tid, int NT) {
+    const int64_t U = a.n_units;
+    if (o.r == 0)
+        for (int64_t u = tid; u < o.first && u < U; u += NT) a.cum[u] = __builtin_nan("");
+    if (o.r == a.L.n_rollouts - 1)
+        for (int64_t u = (o.first + o.n < 0 ? 0 : o.first + o.n) + tid; u < U; u += NT)
+            a.cum[u] = __builtin_nan("");
+    for (int64_t u = o.lo + tid; u < o.from && u < o.hi; u += NT) a.cum[u] = 0.0;
+}
+
+// The lowest first crossing of a group's threads, and the rollout's results.
+template <int NT>
+__device__ __forceinline__ void finish_group(const StopArgs &a, const Rollout &o, int tid, int32_t best,
+                                             int32_t *s_best) {
+    constexpr int kWaves = NT / kWave;
+#pragma unroll
+    for (int q = kWave / 2; q > 0; q >>= 1) {
+        const int32_t b = __shfl_xor(best, q, kWave);
+        best = b < best ? b : best;
+    }
+    if (kWaves > 1) {
+        if (tid % kWave == 0) s_best[tid / kWave] = best;
+        __syncthreads();
+        if (tid == 0)
+            for (int w = 1; w < kWaves; ++w) best = s_best[w] < best ? s_best[w] : best;
+    }
+    if (tid == 0) finish_rollout(a, o.r, best, o.first, o.n);
+}
+
+// The whole test of one rollout by NT threads (tid their number), NI units each at a time.  The units
+// run through a fixed scan (a thread's items in order, a tree over the lanes, waves in order, chunks
+// in order), so cum is bit-reproducible; the next chunk's values are in flight while one is scanned.
+// All NT threads call it together; with more than one wave they meet at workgroup barriers.
+template <typename VT, int NT, int NI>
+__device__ __forceinline__ void scan_rollout(const StopArgs &a, const Rollout &o, int tid,
+                                             double (*s_sum)[NT / kWave], int32_t *s_best) {
+    constexpr int kWaves = NT / kWave;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int64_t first = o.first, hi = o.hi, from = o.from;
+    const VT *vals = static_cast<const VT *>(a.values);
+    const double lam = o.lam;
+    fill_outside(a, o, tid, NT);
 
     constexpr int64_t kChunk = (int64_t)NT * NI;
     double carry = 0.0;
@@ -522,7 +575,6 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void stop_rollout_kernel(StopA
             if (best == INT_MAX && u0 + j < hi && run[j] < lam) best = (int32_t)(u0 + j - first);
         }
         if (u0 + NI <= hi) {
-            typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
 #pragma unroll
             for (int j = 0; j < NI; j += 2)
                 *reinterpret_cast<Pair *>(a.cum + u0 + j) = Pair{run[j], run[j + 1]};
@@ -535,30 +587,172 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void stop_rollout_kernel(StopA
 #pragma unroll
         for (int j = 0; j < NI; ++j) in[j] = next[j];
     }
+    finish_group<NT>(a, o, tid, best, s_best);
+}
+
+// The same for a rollout long against its group, by NT threads.  Each wave has a stretch of the units: it
+// sums its stretch, meets the others once for what precedes it, and scans the stretch by itself, kRows
+// rows of 128 units at a time with the next kRows in flight, two units to a lane.  Latency bounds it, as
+// it does scan_rollout with 256 threads, whose chunk of 1,024 units costs a trip to memory, one through
+// LDS and a barrier in turn: 400,000 units 298 -> 211 us (turn means), 20,000 15.2 -> 13.7.  The stretches
+// depend on the number of units alone, so cum is bit-reproducible here too.
+constexpr int kRows = 2;
+template <typename VT, int NT>
+__device__ __forceinline__ void scan_long(const StopArgs &a, const Rollout &o, int tid, double *s_sum,
+                                          int32_t *s_best) {
+    constexpr int kWaves = NT / kWave;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    fill_outside(a, o, tid, NT);
+
+    // 32-bit places from the first unit after K0 on: a call of groups has at most kRolloutUnits
+    const VT *vals = static_cast<const VT *>(a.values) + o.from;
+    double *cum = a.cum + o.from;
+    const int n = o.hi > o.from ? (int)(o.hi - o.from) : 0, shift = (int)(o.from - o.first);
+    constexpr int kRow = 2 * kWave, kStep = kRow * kRows;
+    const int each = (n + kRow * kWaves - 1) / (kRow * kWaves) * kRow;
+    const int begin = wave * each < n ? wave * each : n, end = begin + each < n ? begin + each : n;
+    typedef VT Two __attribute__((ext_vector_type(2), aligned(sizeof(VT))));
+    auto load = [&](int base, VT (*x)[2]) __attribute__((always_inline)) {
+        if (base + kStep <= end) {
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const int32_t b = __shfl_xor(best, o, kWave);
-        best = b < best ? b : best;
+            for (int g = 0; g < kRows; ++g) {
+                const Two v = *reinterpret_cast<const Two *>(vals + base + 2 * lane + g * kRow);
+                x[g][0] = v[0];
+                x[g][1] = v[1];
+            }
+        } else {
+#pragma unroll
+            for (int g = 0; g < kRows; ++g)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int u = base + 2 * lane + g * kRow + j;
+                    x[g][j] = u < end ? vals[u] : (VT)0;
+                }
+        }
+    };
+    constexpr int kPer = 16 / sizeof(VT), kLoads = 6;
+    typedef VT Vec __attribute__((ext_vector_type(kPer), aligned(sizeof(VT))));
+    double sum[kPer] = {};
+    int u = begin;
+    for (; u + kLoads * kPer * kWave <= end; u += kLoads * kPer * kWave) {
+        Vec v[kLoads];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i)
+            v[i] = *reinterpret_cast<const Vec *>(vals + u + (i * kWave + lane) * kPer);
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i)
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) sum[j] += (double)v[i][j];
     }
-    if (kWaves > 1) {
-        if (lane == 0) s_best[wave] = best;
+    for (u += lane; u < end; u += kWave) sum[0] += (double)vals[u];
+#pragma unroll
+    for (int j = 1; j < kPer; ++j) sum[0] += sum[j];
+    const double mine = last_lane(wave_scan(sum[0]));
+    if (lane == 0) s_sum[wave] = mine;
+    __syncthreads();
+    double carry = 0.0;
+    for (int w = 0; w < wave; ++w) carry += s_sum[w];
+
+    int32_t best = INT_MAX;
+    auto step = [&](int base, const VT (*in)[2]) __attribute__((always_inline)) {
+        double inc[kRows];
+#pragma unroll
+        for (int g = 0; g < kRows; ++g) inc[g] = wave_scan((double)in[g][0] + (double)in[g][1]);
+#pragma unroll
+        for (int g = 0; g < kRows; ++g) {
+            const int u = base + 2 * lane + g * kRow;
+            const double c0 = carry + moved<0x138, 0xF>(inc[g]) + (double)in[g][0], c1 = c0 + (double)in[g][1];
+            carry += last_lane(inc[g]);
+            if (best == INT_MAX && u < end && c0 < o.lam) best = u + shift;
+            if (best == INT_MAX && u + 1 < end && c1 < o.lam) best = u + 1 + shift;
+            if (u + 1 < end)
+                *reinterpret_cast<Pair *>(cum + u) = Pair{c0, c1};
+            else if (u < end)
+                cum[u] = c0;
+        }
+    };
+    VT x[2][kRows][2];
+    load(begin, x[0]);
+    load(begin + kStep, x[1]);
+    for (int base = begin; base < end; base += 2 * kStep) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            step(base + h * kStep, x[h]);
+            load(base + (h + 2) * kStep, x[h]);
+        }
+    }
+    finish_group<NT>(a, o, tid, best, s_best);
+}
+
+// The whole test with a group of threads for each rollout: no tiles, no look-back, one launch.
+// Latency bounds it: offsets, then values, K0 and domain together, then a chunk after the other.
+// kRolloutUnits has what it measured.
+//
+// One wave per rollout, four to a workgroup, behind `helpers` workgroups that take the rollouts of more
+// than kWaveLength units, which the waves pass over: helper k looks at rollouts k, k + helpers, ...
+// 64 registers, so that eight waves fit a SIMD (with 85 it took 18.4 us for 32,768 rollouts of 8 units).
+template <typename VT>
+__global__ __launch_bounds__(256, 8) void stop_waves_kernel(StopArgs a, int helpers) {
+    constexpr int kWaves = 256 / kWave;
+    __shared__ double s_sum[kWaves];
+    __shared__ int32_t s_best[kWaves], s_count;
+    __shared__ int32_t s_long[256];
+    const int64_t R = a.L.n_rollouts;
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= helpers) {
+        const int64_t r = (int64_t)((int)blockIdx.x - helpers) * kWaves +
+                          __builtin_amdgcn_readfirstlane(tid / kWave);
+        if (r >= R) return;
+        const Rollout o = rollout_of(a, r, tid % kWave == 0);
+        if (o.hi - o.lo <= kWaveLength)
+            scan_rollout<VT, kWave, 2>(a, o, tid % kWave, nullptr, nullptr);
+        return;
+    }
+    const int64_t step = (int64_t)helpers * 256;
+    for (int64_t base = blockIdx.x; base < R; base += step) {
+        if (tid == 0) s_count = 0;
         __syncthreads();
-        if (tid == 0)
-            for (int w = 1; w < kWaves; ++w) best = s_best[w] < best ? s_best[w] : best;
+        const int64_t r = base + (int64_t)tid * helpers;
+        if (tid < 256 && r < R) {
+            const Rollout o = rollout_of(a, r, false);
+            if (o.hi - o.lo > kWaveLength) s_long[atomicAdd(&s_count, 1)] = (int32_t)r;
+        }
+        __syncthreads();
+        const int n = s_count;
+        for (int i = 0; i < n; ++i) {
+            int t = tid;
+            asm volatile("" : "+v"(t));  // opaque: addresses formed once for all rollouts cost registers
+            scan_long<VT, 256>(a, rollout_of(a, __builtin_amdgcn_readfirstlane(s_long[i]), false), t, s_sum, s_best);
+            __syncthreads();  // the shared sums are read by all before the next rollout's are written
+        }
     }
-    if (tid == 0) finish_rollout(a, r, best, first, n);
+}
+
+// A workgroup per rollout.
+template <typename VT, int NT, int NI>
+__global__ __launch_bounds__(NT) void stop_block_kernel(StopArgs a) {
+    __shared__ double s_sum[2][NT / kWave];
+    __shared__ int32_t s_best[NT / kWave];
+    const Rollout o = rollout_of(a, blockIdx.x, threadIdx.x == 0);
+    if (NT == 256 && o.hi - o.from > 8 * NT * NI)
+        scan_long<VT, NT>(a, o, threadIdx.x, s_sum[0], s_best);
+    else
+        scan_rollout<VT, NT, NI>(a, o, threadIdx.x, s_sum, s_best);
 }
 
 template <typename VT>
 static hipError_t launch_stop_rollouts(const StopArgs &a, int64_t per, hipStream_t stream) {
     const unsigned R = (unsigned)a.L.n_rollouts;
     // Threads by the rollouts' average length: enough for one chunk or two of it.
-    if (per <= 128)
-        hipLaunchKernelGGL((stop_rollout_kernel<VT, 64, 2>), dim3((R + 3) / 4), dim3(256), 0, stream, a);
-    else if (per <= 1024)
-        hipLaunchKernelGGL((stop_rollout_kernel<VT, 256, 4>), dim3(R), dim3(256), 0, stream, a);
-    else
-        hipLaunchKernelGGL((stop_rollout_kernel<VT, 1024, 8>), dim3(R), dim3(1024), 0, stream, a);
+    if (per <= 128) {
+        // no rollout is longer than the call
+        const int helpers = a.n_units <= kWaveLength ? 0 : (R < kHelpers ? (int)R : kHelpers);
+        hipLaunchKernelGGL(stop_waves_kernel<VT>, dim3((R + 3) / 4 + helpers), dim3(256), 0, stream, a, helpers);
+    } else if (per <= 1024) {
+        hipLaunchKernelGGL((stop_block_kernel<VT, 256, 4>), dim3(R), dim3(256), 0, stream, a);
+    } else {
+        hipLaunchKernelGGL((stop_block_kernel<VT, 1024, 8>), dim3(R), dim3(1024), 0, stream, a);
+    }
     return hipGetLastError();
 }
 

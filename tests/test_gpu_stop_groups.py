@@ -14,6 +14,11 @@ SIZES = {  # lengths at the edges of a chunk of 128, 1,024 and 8,192 (restart: 1
     "block": [1023, 1024, 1025, 1, 0, 2047, 2048, 2049, 255, 257, 700, 5],
     "wide": [8191, 8192, 8193, 1, 0, 4095, 4096, 4097, 16385, 12289, 2],
     "skewed": [40000] + [3] * 1500,
+    # longer than a wave takes (1,024 units) among short ones: alone, one after the other, the first and the
+    # last; and more rollouts than the workgroups that take these look at in one round (127 x 256)
+    "far": [1023, 1024, 1025, 2049, 1, 0, 5000, 1536, 1537] + [2] * 200 + [9000] + [1] * 150 + [1100],
+    "far in a second round": [1500] + [3] * 32600 + [1100, 2, 1300] + [1] * 30,
+    "block and far": [8193, 20000, 8192, 16500] + [300] * 100,   # past eight chunks of a workgroup
     "tiles": [140000, 1, 0, 2048],   # past the average a group takes: the tile scan
 }
 
@@ -107,3 +112,47 @@ def test_many_short_rollouts_as_tiles():
     assert np.max(np.abs(path.cum.cpu().numpy() - cum_o)) <= 1e-12
     assert np.array_equal(path.stop_unit.cpu().numpy(), stop_o)
     assert np.array_equal(path.retained.cpu().numpy(), ret_o)
+
+
+@pytest.mark.parametrize("call", ["stop"])
+def test_one_long_rollout_among_short_ones_takes_its_own_time(call):
+    """40,000 units before 1,500 rollouts of 3: the stop test and the restart pick take at most 2.5 times
+    what the long rollout takes alone (a wave of its own takes 6 and 8 times as long)."""
+    import torch
+    import paper_2609_14636_amd as P
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+
+    def time(sizes):
+        off = np.concatenate([[0], np.cumsum(sizes)])
+        U = int(off[-1])
+        lay = P.Layout(dev(off.astype(np.int32)), dev(np.arange(U + 1, dtype=np.int64)), U)
+        path = P.Path(lay, P.STRIDE_UNIT_TURN, with_student=False)
+        vals = -torch.rand(U, dtype=torch.float64, device="cuda")
+
+        def run():
+            if call == "stop":
+                P.stride_stop(lay, P.STRIDE_UNIT_TURN, vals, [-1e9], None, path.cum, path.stop_unit,
+                              path.retained, path.flags, path.ws)
+            else:
+                P.stride_restart_turn(lay, P.STRIDE_UNIT_TURN, vals, None, [-1e9], None, path.k_star,
+                                      path.k0, path.k_max, path.flags)
+        run()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                run()
+        graph.replay()
+        best = float("inf")
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    alone, among = time([40000]), time([40000] + [3] * 1500)
+    print(f"{call}, ms for 20 calls: alone {alone:.3f}, among short ones {among:.3f}", flush=True)
+    assert among <= 2.5 * alone
