@@ -8,8 +8,8 @@
 // The record is the rollout's units up to and including its stop (Algorithm 1
 // records the generated turns).  Ties go to the lowest index.
 //
-// One workgroup per rollout reads the record once, in chunks of eight units per
-// thread (eight loads in flight): a block-wide integer min finds the chunk's first
+// A wave or a workgroup per rollout reads the record once, in chunks of two or eight units per
+// thread (their loads in flight together): an integer min over its threads finds the chunk's first
 // non-correct unit, the units before it join the lexicographic min of
 // (value, index), and the first chunk that has one ends the search.  The pick is
 // exact and deterministic.
@@ -19,6 +19,14 @@
 
 namespace stride {
 namespace {
+
+// Where the average rollout has at most 128 units, one wave takes each record of up to kWaveLength units
+// (two of its chunks of 512) and kHelpers workgroups of the same launch the longer ones: 40,000 units
+// before 1,500 rollouts of 3 took a wave 162 us and take a helper 23.8 (one workgroup of 256 for every
+// rollout and two passes: 43.7).  A prime number of helpers, so that long rollouts at regular places are
+// spread over them.
+constexpr int64_t kWaveLength = 1024;
+constexpr int kHelpers = 127;
 
 struct RestartArgs {
     stride_layout L;
@@ -34,25 +42,14 @@ struct RestartArgs {
     uint32_t *flags;
 };
 
-// NT threads per rollout, by the rollouts' average length: one wave of a 256-thread workgroup
-// up to 128 units, a workgroup of 256 up to 1,024, of 512 above (which also has the next chunk's
-// values in flight: 5.4 us against 5.0 where 256 threads need no second chunk).  Latency bounds
-// the kernel (a chunk costs a round trip to memory and two barriers), and for many short rollouts
-// the number of workgroups.  Measured against 256 threads for every rollout and two passes:
-// 8 x 16,384 units 38.0 -> 16.1 us (1,024 threads 14.0, but 9.1 against 7.2 where the first chunk
-// ends the search; 512 threads 7.6), 64 x 4,096 14.5 -> 8.4, 8 x 8 5.2 -> 3.8, 20,000 x 12
-// 41.7 -> 12.1, 200,000 x 3 398 -> 83.
-template <typename VT, int NT>
-__global__ __launch_bounds__(NT < 256 ? 256 : NT) void restart_kernel(RestartArgs a) {
-    static_assert(NT == kWave || NT >= 256, "a group is one wave or a whole workgroup");
-    constexpr int kGroups = NT == kWave ? 4 : 1, kWaves = NT / kWave;
-    constexpr int PU = NT == kWave ? 2 : 8;  // units per thread and chunk
-    __shared__ int64_t s_min;
-    __shared__ double s_val[kWaves];
-    __shared__ int64_t s_idx[kWaves];
-    const int64_t r = (int64_t)blockIdx.x * kGroups + __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
-    if (r >= a.L.n_rollouts) return;
-    const int tid = threadIdx.x % NT, lane = tid & (kWave - 1), wave = tid / kWave;
+// A rollout's record: its first unit and its length, -1 where the offsets or the domain are bad.
+struct Record {
+    int64_t first, len;
+    double alpha;
+};
+
+// With `report`, a rollout without a record gets its results and flag here.
+__device__ __forceinline__ Record record_of(const RestartArgs &a, int64_t r, bool report) {
     const int64_t T = a.L.n_turns;
     const int64_t t0 = a.L.rollout_turn_off[r], t1 = a.L.rollout_turn_off[r + 1];
     const int32_t d = a.L.domain ? a.L.domain[r] : 0, s = a.stop_unit ? a.stop_unit[r] : -1;
@@ -70,24 +67,31 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void restart_kernel(RestartArg
     }
     const bool bad_dom = d < 0 || d >= a.n_dom;
     if (bad_off || bad_dom) {
-        if (tid == 0) {
+        if (report) {
             a.k_star[r] = -1;
             a.k0[r] = 0;
             if (a.k_max) a.k_max[r] = 0;
             raise_flag(a.flags, bad_off ? STRIDE_FLAG_BAD_OFFSETS : STRIDE_FLAG_BAD_DOMAIN);
         }
-        return;
+        return Record{0, -1, 0.0};
     }
-    int64_t len = n;
-    if (s >= 0 && (int64_t)s + 1 < n) len = (int64_t)s + 1;
-    const double alpha = a.alpha.v[d];
-    const VT *vals = static_cast<const VT *>(a.values);
+    return Record{first, s >= 0 && (int64_t)s + 1 < n ? (int64_t)s + 1 : n, a.alpha.v[d]};
+}
 
-    // ---- K_max = first non-correct unit in [0, len), else len; lowest index of the minimum
-    // over [0, K_max) ----
+// One rollout by NT threads (tid their number), PU units each at a time; with more than one wave
+// they meet at workgroup barriers.  K_max = first non-correct unit in [0, len), else len; k* = lowest
+// index of the minimum over [0, K_max).
+template <typename VT, int NT, int PU>
+__device__ __forceinline__ void pick(const RestartArgs &a, int64_t r, const Record &rec, int tid,
+                                     int64_t *s_min, double *s_val, int64_t *s_idx) {
+    constexpr int kWaves = NT / kWave;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int64_t first = rec.first, len = rec.len;
+    const double alpha = rec.alpha;
+    const VT *vals = static_cast<const VT *>(a.values);
     int64_t kmax = len;
     if (kWaves > 1) {
-        if (tid == 0) s_min = len;
+        if (tid == 0) *s_min = len;
         __syncthreads();
     }
     double best = __builtin_inf();
@@ -95,11 +99,21 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void restart_kernel(RestartArg
     VT v[PU], v2[PU];
     uint8_t mk[PU], mk2[PU];
     auto fetch = [&](int64_t c, VT *x, uint8_t *m) __attribute__((always_inline)) {
+        const VT *p = vals + first + c + tid;
+        if (c + (int64_t)NT * PU <= len) {  // a whole chunk: no load waits for another's bound
 #pragma unroll
-        for (int k = 0; k < PU; ++k) {
-            const int64_t u = c + (int64_t)k * NT + tid;
-            x[k] = u < len ? vals[first + u] : (VT)0;
-            m[k] = u < len && a.mask ? a.mask[first + u] : 1;
+            for (int k = 0; k < PU; ++k) x[k] = p[k * NT];
+        } else {
+#pragma unroll
+            for (int k = 0; k < PU; ++k) x[k] = c + k * NT + tid < len ? p[k * NT] : (VT)0;
+        }
+#pragma unroll
+        for (int k = 0; k < PU; ++k) m[k] = 1;
+        if (a.mask) {
+            const uint8_t *q = a.mask + first + c + tid;
+#pragma unroll
+            for (int k = 0; k < PU; ++k)
+                if (c + k * NT + tid < len) m[k] = q[k * NT];
         }
     };
     constexpr bool kAhead = NT > 256;  // the next chunk's values in flight while this one is looked at
@@ -123,9 +137,9 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void restart_kernel(RestartArg
             }
             kmax = wrong < len ? wrong : len;
         } else {
-            if (wrong != LLONG_MAX) atomicMin((unsigned long long *)&s_min, (unsigned long long)wrong);
+            if (wrong != LLONG_MAX) atomicMin((unsigned long long *)s_min, (unsigned long long)wrong);
             __syncthreads();
-            kmax = s_min;
+            kmax = *s_min;
         }
 #pragma unroll
         for (int k = 0; k < PU; ++k) {
@@ -178,14 +192,77 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void restart_kernel(RestartArg
     }
 }
 
+// NT threads per rollout, by the rollouts' average length: one wave of a 256-thread workgroup
+// up to 128 units, a workgroup of 256 up to 1,024, of 512 above (which also has the next chunk's
+// values in flight: 5.4 us against 5.0 where 256 threads need no second chunk).  Latency bounds
+// the kernels (a chunk costs a round trip to memory and two barriers), and for many short rollouts
+// the number of workgroups.  Measured against 256 threads for every rollout and two passes:
+// 8 x 16,384 units 34.2 -> 16.2 us (1,024 threads 14.0, but 9.1 against 7.2 where the first chunk
+// ends the search), 64 x 4,096 11.6 -> 7.1, 8 x 8 4.6 -> 3.6, 20,000 x 12 37.9 -> 10.7,
+// 200,000 x 3 398 -> 83.
+//
+// One wave per rollout, four to a workgroup, behind `helpers` workgroups that take the records of more
+// than kWaveLength units, which the waves pass over: helper k looks at rollouts k, k + helpers, ...
 template <typename VT>
-void launch_restart_groups(const RestartArgs &a, unsigned R, int64_t per, hipStream_t stream) {
-    if (per <= 128)
-        hipLaunchKernelGGL((restart_kernel<VT, 64>), dim3((R + 3) / 4), dim3(256), 0, stream, a);
-    else if (per <= 1024)
-        hipLaunchKernelGGL((restart_kernel<VT, 256>), dim3(R), dim3(256), 0, stream, a);
+__global__ __launch_bounds__(256) void restart_waves_kernel(RestartArgs a, int helpers) {
+    constexpr int kWaves = 256 / kWave;
+    __shared__ int64_t s_min, s_idx[kWaves];
+    __shared__ double s_val[kWaves];
+    __shared__ int32_t s_count;
+    __shared__ int32_t s_long[256];
+    const int64_t R = a.L.n_rollouts;
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= helpers) {
+        const int64_t r = (int64_t)((int)blockIdx.x - helpers) * kWaves +
+                          __builtin_amdgcn_readfirstlane(tid / kWave);
+        if (r >= R) return;
+        const Record rec = record_of(a, r, tid % kWave == 0);
+        if (rec.len < 0 || rec.len > kWaveLength) return;
+        if (rec.len <= 2 * kWave)
+            pick<VT, kWave, 2>(a, r, rec, tid % kWave, nullptr, nullptr, nullptr);
+        else
+            pick<VT, kWave, 8>(a, r, rec, tid % kWave, nullptr, nullptr, nullptr);
+        return;
+    }
+    const int64_t step = (int64_t)helpers * 256;
+    for (int64_t base = blockIdx.x; base < R; base += step) {
+        if (tid == 0) s_count = 0;
+        __syncthreads();
+        const int64_t r = base + (int64_t)tid * helpers;
+        if (r < R) {
+            if (record_of(a, r, false).len > kWaveLength) s_long[atomicAdd(&s_count, 1)] = (int32_t)r;
+        }
+        __syncthreads();
+        const int n = s_count;
+        for (int i = 0; i < n; ++i) {
+            int t = tid;
+            asm volatile("" : "+v"(t));  // opaque: addresses formed once for all records cost registers
+            const int64_t far = __builtin_amdgcn_readfirstlane(s_long[i]);
+            pick<VT, 256, 8>(a, far, record_of(a, far, false), t, &s_min, s_val, s_idx);
+            __syncthreads();  // the shared values are read by all before the next record's are written
+        }
+    }
+}
+
+template <typename VT, int NT>
+__global__ __launch_bounds__(NT) void restart_block_kernel(RestartArgs a) {
+    __shared__ int64_t s_min, s_idx[NT / kWave];
+    __shared__ double s_val[NT / kWave];
+    const Record rec = record_of(a, blockIdx.x, threadIdx.x == 0);
+    if (rec.len >= 0) pick<VT, NT, 8>(a, blockIdx.x, rec, threadIdx.x, &s_min, s_val, s_idx);
+}
+
+template <typename VT>
+void launch_restart_groups(const RestartArgs &a, unsigned R, int64_t n_units, hipStream_t stream) {
+    const int64_t per = n_units / R;
+    if (per <= 128) {
+        // no record is longer than the call
+        const int helpers = n_units <= kWaveLength ? 0 : (R < (unsigned)kHelpers ? (int)R : kHelpers);
+        hipLaunchKernelGGL(restart_waves_kernel<VT>, dim3((R + 3) / 4 + helpers), dim3(256), 0, stream, a, helpers);
+    } else if (per <= 1024)
+        hipLaunchKernelGGL((restart_block_kernel<VT, 256>), dim3(R), dim3(256), 0, stream, a);
     else
-        hipLaunchKernelGGL((restart_kernel<VT, 512>), dim3(R), dim3(512), 0, stream, a);
+        hipLaunchKernelGGL((restart_block_kernel<VT, 512>), dim3(R), dim3(512), 0, stream, a);
 }
 
 }  // namespace
@@ -208,12 +285,11 @@ hipError_t launch_restart(const stride_layout &L, int32_t unit, const void *valu
     a.k_max = k_max;
     a.flags = flags;
     const int64_t n_units = unit == STRIDE_UNIT_TURN ? L.n_turns : L.n_tokens;
-    const int64_t per = n_units / L.n_rollouts;
     const unsigned R = (unsigned)L.n_rollouts;
     if (unit == STRIDE_UNIT_TURN)
-        launch_restart_groups<double>(a, R, per, stream);
+        launch_restart_groups<double>(a, R, n_units, stream);
     else
-        launch_restart_groups<float>(a, R, per, stream);
+        launch_restart_groups<float>(a, R, n_units, stream);
     return hipGetLastError();
 }
 

@@ -114,7 +114,7 @@ def test_many_short_rollouts_as_tiles():
     assert np.array_equal(path.retained.cpu().numpy(), ret_o)
 
 
-@pytest.mark.parametrize("call", ["stop"])
+@pytest.mark.parametrize("call", ["stop", "restart"])
 def test_one_long_rollout_among_short_ones_takes_its_own_time(call):
     """40,000 units before 1,500 rollouts of 3: the stop test and the restart pick take at most 2.5 times
     what the long rollout takes alone (a wave of its own takes 6 and 8 times as long)."""
