@@ -467,6 +467,7 @@ __device__ __forceinline__ void fused_rows(const FusedArgs &a) {
         for (int i = 0; i < kHLoads; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rh, LDS_PTR(dst + i * 8 * kRowB), 16, hoff[i],
                                                      k * kRowB, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);  // the waits below count on H's loads ahead of W's
         // blocks past the share lie past the descriptor: zeros, and no memory traffic
         const int blk = iq * per + wave;
         const int base = wave < per && blk < cnt ? blk * kShareRows * d * 2 : 0x7f000000;
@@ -476,6 +477,7 @@ __device__ __forceinline__ void fused_rows(const FusedArgs &a) {
             for (int hf = 0; hf < 2; ++hf)
                 wreg[slot][mb][hf] = __builtin_amdgcn_raw_buffer_load_b128(
                     rw, base + woff + mb * 16 * d * 2 + hf * 64, k * kRowB, 0);
+        __builtin_amdgcn_sched_barrier(0);
         if (++ij == ns) {
             ij = 0;
             ++iq;
