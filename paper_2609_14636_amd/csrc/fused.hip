@@ -68,6 +68,9 @@ constexpr int kHalf = 128;                         // vocabulary entries per par
 constexpr int64_t kBandHBytes = 128ll << 20;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.69314718055994531f;
+// Lowest reference point of a (max, sum): times log2(e) it is still finite in fp32, so logits below it
+// add nothing to the row, whether or not the others of their partial are as low.
+constexpr float kLowestRef = -2.358e38f;
 // Third word of a raw buffer descriptor: 32-bit data format, no swizzle; accesses
 // at or beyond num_records bytes return zeros.
 constexpr int kBufferFlags = 0x00020000;
@@ -357,8 +360,7 @@ __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
         for (int x = 1; x < 4 * NB; ++x) m = fmaxf(m, acc[x >> 2][jj][x & 3]);
         m = fmaxf(m, __shfl_xor(m, 16, 64));
         m = fmaxf(m, __shfl_xor(m, 32, 64));
-        const float ref = (m == -INFINITY) ? 0.0f : m;
-        const float mref = ref * kLog2e;
+        const float mref = fmaxf(m, kLowestRef) * kLog2e;
         float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
         for (int x = 0; x < 4 * NB; x += 2) {
@@ -547,7 +549,7 @@ __device__ __forceinline__ void fused_rows(const FusedArgs &a) {
                     for (int x = 1; x < 8; ++x) m = fmaxf(m, z[x]);
                     m = fmaxf(m, __shfl_xor(m, 16, 64));
                     m = fmaxf(m, __shfl_xor(m, 32, 64));
-                    const float mref = ((m == -INFINITY) ? 0.0f : m) * kLog2e;
+                    const float mref = fmaxf(m, kLowestRef) * kLog2e;
                     float sum = 0.0f;
 #pragma unroll
                     for (int x = 0; x < 8; ++x) sum += ex2(__builtin_fmaf(z[x], kLog2e, -mref));

@@ -122,6 +122,32 @@ def test_fused_few_rows(rows, vocab, d):
     assert np.max(np.abs(path.logp_t.cpu().numpy() - sc["logp_t"])) <= H.TOL_LOGP
 
 
+@pytest.mark.parametrize("rows", [20, 100, 140, 200, 300])
+def test_fused_logits_at_the_lowest_values(rows):
+    """Weight rows that take their logits to -3e38 leave the row's log-probability as it is without them,
+    whether they fill a partial of 32 entries or share one with others."""
+    import torch
+    import paper_2609_14636_amd as P
+    V, d = 1000, 64
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    h = torch.rand((rows, d), device="cuda", generator=g).add_(0.5).to(torch.bfloat16)
+    w = torch.empty((V, d), device="cuda").normal_(0, 0.3, generator=g).to(torch.bfloat16)
+    low = torch.zeros(V, dtype=torch.bool, device="cuda")
+    low[64:96] = low[128:256] = low[300:310] = low[-8:] = True
+    z = h.float().sum(1)
+    w[low] = torch.tensor(-3e38, device="cuda").div(z.max()).to(torch.bfloat16)
+    keep = (~low).nonzero().squeeze(1)
+    ids = keep[torch.randint(0, keep.numel(), (rows,), device="cuda", generator=g)].int()
+    lay = P.Layout(torch.tensor([0, 1], dtype=torch.int32, device="cuda"),
+                   torch.tensor([0, rows], dtype=torch.int64, device="cuda"), rows)
+    path = P.Path(lay, P.STRIDE_UNIT_TURN, with_student=False, fused_vocab=V)
+    path.score_fused(V, h, w, None, ids)
+    assert int(path.flags.item()) == 0
+    want = (h.double() @ w[keep].double().t()).log_softmax(1)
+    want = want.gather(1, torch.searchsorted(keep, ids.long()).unsqueeze(1)).squeeze(1)
+    assert float((path.logp_t.double() - want).abs().max()) <= H.TOL_LOGP
+
+
 def test_fused_random_shapes():
     """Thirty random small shapes against the oracle: 1 to 1,200 rows (partial row tiles),
     vocabularies of 1 to 5,000 entries (partial 128- and 256-column tiles) and hidden sizes of one
