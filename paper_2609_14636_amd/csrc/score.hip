@@ -581,11 +581,16 @@ hipError_t launch_rows_form(const ScoreArgs &a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// The form by the row's 16-byte words and the number of rows.  More wavefronts per row read fewer
+// The form by the row's 16-byte words and the number of row items (teacher and student rows, called rows
+// below).  More wavefronts per row read fewer
 // rows at a time, and leave less of the chip idle at the end, but each needs words enough for its
 // loads.  Teacher and student rows, bf16, one wavefront per row -> the form taken here:
 //   words    8, 32,768 rows: 23.6 -> 21.2 us (28.4 with the folds of words that are not there)
 //   words  125, 60,000 rows: 57.6 -> 36.1 us (U = 4 instead of 8; eight wavefronts 131)
+//   words 1,000: 32 rows 6.2 -> 5.6 us, 512 rows 7.2 -> 6.1, 2,048 rows 15.2 -> 9.3 (four wavefronts; one
+//                7.8, 9.0 and 10.2, but 26.0 against 27.3 at 8,192); words 300: 512 rows 6.2 -> 5.9 (one 6.6),
+//                2,048 rows 10.5 -> 7.1 (four 7.7).  These and the next are graph replays with the turn mean
+//   words 1,030: 80,000 rows 219 -> 217 us (U = 8 leaves two of four wavefronts without a chunk: 252)
 //   words 2,000, 60,000 rows: 282 -> 274 us; 2,000 rows 13.8 -> 12.5
 //   words 4,000, 60,000 rows: 561 -> 524 us; words 6,250, 32,768 rows: 480 -> 458
 //   words 12,500, 80,000 rows: 2,368 -> 2,252 us (U = 8, one chunk at a time: 2,260)
@@ -602,7 +607,11 @@ hipError_t launch_rows(const ScoreArgs &a, hipStream_t stream) {
     const int words = a.vocab / Elem<DT>::kPerVec;
     const int64_t items = a.student ? 2 * a.n_rows : a.n_rows;
     const bool many = items >= 16384;
-    if (words < 1024) return launch_rows_form<DT, 1, 8, 4, 1>(a, stream);
+    if (words < 1024) {
+        if (items <= (words < 512 ? 1024 : 2048)) return launch_rows_form<DT, 4, 1, 4, 1>(a, stream);
+        return launch_rows_form<DT, 1, 8, 4, 1>(a, stream);
+    }
+    if (DT == STRIDE_BF16 && words < 1408) return launch_rows_form<DT, 4, 1, 4, 1>(a, stream);
     if (words < 3072) return launch_rows_form<DT, 4, 1, 8, 1>(a, stream);
     if (words < 8192) return launch_rows_form<DT, 8, 1, 8, 1>(a, stream);
     if (DT == STRIDE_BF16 && items >= 196608 && words >= 16384 && words < 24576)

@@ -195,3 +195,16 @@ def test_masks_of_the_lowest_value(dtype, exact_kl):
     for words, n, masked in MASKED:
         print("words", words, "rows", n, "masked", masked, flush=True)
         _masked(words, n, torch.bfloat16 if dtype == "bf16" else torch.float32, masked, exact_kl)
+
+
+# words, rows: both sides of the borders by the number of rows (1,024 or 2,048) and by the words (1,408)
+BORDERS = [(511, 1024), (511, 1025), (512, 1024), (512, 2048), (512, 2049), (1023, 2048), (1023, 2049),
+           (1024, 40), (1407, 300), (1408, 300), (3, 1024), (3, 1025)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_borders_by_the_number_of_rows(dtype):
+    import torch
+    for words, n in BORDERS:
+        print("words", words, "rows", n, flush=True)
+        _check(words, n, torch.bfloat16 if dtype == "bf16" else torch.float32, 3)
