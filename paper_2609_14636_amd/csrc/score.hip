@@ -203,21 +203,16 @@ __global__ __launch_bounds__(W *RW *kWave) void score_rows_kernel(ScoreArgs a) {
         for (int u = 0; u < U; ++u) unpack<DT>(v[u], x + u * E);
         fold<U * E>(m, s0, s1, x);
     };
-    // words after the last whole chunk, every W-th block of 64 of them; -inf past the row.  Fetched
-    // first, unless they are so many that holding them through the row costs occupancy.
+    // words after the last whole chunk, every W-th block of 64 of them; -inf past the row
     constexpr int kRest = (U + W - 1) / W;
-    constexpr bool kRestFirst = kRest <= 4;
     u32x4 rest[kRest];
-    auto load_rest = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < kRest; ++i) {
-            const int k = nfull * kStep + (i * W + wave) * kWave + lane;
-            constexpr uint32_t n = Elem<DT>::kNegInf;
-            rest[i] = u32x4{n, n, n, n};
-            if (k < nvec) rest[i] = __builtin_nontemporal_load(p + k);
-        }
-    };
-    if (kRestFirst) load_rest();
+    for (int i = 0; i < kRest; ++i) {
+        const int k = nfull * kStep + (i * W + wave) * kWave + lane;
+        constexpr uint32_t n = Elem<DT>::kNegInf;
+        rest[i] = u32x4{n, n, n, n};
+        if (k < nvec) rest[i] = __builtin_nontemporal_load(p + k);
+    }
     u32x4 v[D][U];
     if (D == 1) {
         for (int i = 0; i < mine; ++i) {
@@ -243,7 +238,6 @@ __global__ __launch_bounds__(W *RW *kWave) void score_rows_kernel(ScoreArgs a) {
             if (i + d < mine) use(v[d % D]);
         }
     }
-    if (!kRestFirst) load_rest();
 #pragma unroll
     for (int i = 0; i < kRest; ++i) {
         if (nfull * kStep + (i * W + wave) * kWave >= nvec) break;  // the same for the whole wavefront
@@ -582,9 +576,8 @@ hipError_t launch_rows_form(const ScoreArgs &a, hipStream_t stream) {
 }
 
 // The form by the row's 16-byte words and the number of row items (teacher and student rows, called rows
-// below).  More wavefronts per row read fewer
-// rows at a time, and leave less of the chip idle at the end, but each needs words enough for its
-// loads.  Teacher and student rows, bf16, one wavefront per row -> the form taken here:
+// below).  More wavefronts per row read fewer rows at a time, and leave less of the chip idle at the end,
+// but each needs words enough for its loads.  Teacher and student rows, bf16, one wavefront per row -> the form taken here:
 //   words    8, 32,768 rows: 23.6 -> 21.2 us (28.4 with the folds of words that are not there)
 //   words  125, 60,000 rows: 57.6 -> 36.1 us (U = 4 instead of 8; eight wavefronts 131)
 //   words 1,000: 32 rows 6.2 -> 5.6 us, 512 rows 7.2 -> 6.1, 2,048 rows 15.2 -> 9.3 (four wavefronts; one
@@ -593,30 +586,32 @@ hipError_t launch_rows_form(const ScoreArgs &a, hipStream_t stream) {
 //   words 1,030: 80,000 rows 219 -> 217 us (U = 8 leaves two of four wavefronts without a chunk: 252)
 //   words 2,000, 60,000 rows: 282 -> 274 us; 2,000 rows 13.8 -> 12.5
 //   words 4,000, 60,000 rows: 561 -> 524 us; words 6,250, 32,768 rows: 480 -> 458
+//   words 8,300: 128 rows 9.1 -> 9.0 us (three chunks of U = 4 in flight, the form of more rows, 10.1);
+//                words 18,992: 512 rows 27.1 us either way (27.5), 8,192 rows 365 (357)
 //   words 12,500, 80,000 rows: 2,368 -> 2,252 us (U = 8, one chunk at a time: 2,260)
 //   words 18,992: 128 rows 58 -> 11 us, 8,192 rows 383 -> 362 (sixteen wavefronts 366),
-//                 32,768 rows 1,444 -> 1,425 (eight 1,435), 174,554 rows 7,681 -> 7,637 (7,669)
-// Sixteen wavefronts pay at two or three of their rounds of 8,192 words: 1,201 against 1,211 us
-// at 16,384 words, 1% slower than eight at 25,000.  fp32 rows hold half the arithmetic per word and
-// leave registers for two such workgroups per CU: sixteen from 8,192 words on (853 against 869 us
-// at 12,500 words, 30,000 rows).  From 196,608 rows of those lengths on one wavefront per row keeps up
-// on a warm card (262,144 rows 11,904 us against 11,696) and is ahead on a cool one (11,398 against
-// 11,614), so it stays there.
+//                 32,768 rows 1,444 -> 1,425 (eight 1,435), 174,554 rows 7,681 -> 7,637 (7,669),
+//                 196,608 rows 9,052 -> 8,931, 262,144 rows 11,736 -> 11,719
+// Sixteen wavefronts at 48,000 rows, alternating with one and with eight: 0.943 and 0.960 of one's time at
+// 16,200 words, 0.948 and 0.960 at 17,200, 0.953 and 0.965 at 19,800, 0.956 and 0.975 at 20,800; but
+// 0.966 and 0.959 at 12,000, 1.06 and 0.943 at 9,000.  These rows start on 128-byte lines.  Off them
+// eight are ahead, 1.003 and 0.987 at 16,700 words, 1.001 and 0.979 at 19,300: two wavefronts then share a
+// line at each chunk's edge, and may both read it.  fp32 rows hold half the arithmetic per word and leave registers for two such workgroups per CU: sixteen from 8,448 words on,
+// on lines or off them (853 against 869 us at 12,500 words, 30,000 rows; 1.04 of one wavefront's time
+// at 8,192 words, where eight take 1.00).
 template <int DT>
 hipError_t launch_rows(const ScoreArgs &a, hipStream_t stream) {
     const int words = a.vocab / Elem<DT>::kPerVec;
     const int64_t items = a.student ? 2 * a.n_rows : a.n_rows;
-    const bool many = items >= 16384;
     if (words < 1024) {
         if (items <= (words < 512 ? 1024 : 2048)) return launch_rows_form<DT, 4, 1, 4, 1>(a, stream);
         return launch_rows_form<DT, 1, 8, 4, 1>(a, stream);
     }
     if (DT == STRIDE_BF16 && words < 1408) return launch_rows_form<DT, 4, 1, 4, 1>(a, stream);
     if (words < 3072) return launch_rows_form<DT, 4, 1, 8, 1>(a, stream);
-    if (words < 8192) return launch_rows_form<DT, 8, 1, 8, 1>(a, stream);
-    if (DT == STRIDE_BF16 && items >= 196608 && words >= 16384 && words < 24576)
-        return launch_rows_form<STRIDE_BF16, 1, 8, 8, 1>(a, stream);
-    if (many && (DT == STRIDE_F32 || (words >= 16384 && words < 24576)))
+    if (words < 8192 || items < 4096) return launch_rows_form<DT, 8, 1, 8, 1>(a, stream);
+    const bool lines = a.ld * Elem<DT>::kSize % 128 == 0;
+    if (items >= 16384 && (DT == STRIDE_F32 ? words >= 8448 : (lines && words >= 16384 && words < 24576)))
         return launch_rows_form<DT, 16, 1, 8, 1>(a, stream);
     return launch_rows_form<DT, 8, 1, 4, 3>(a, stream);
 }

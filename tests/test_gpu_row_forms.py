@@ -208,3 +208,12 @@ def test_borders_by_the_number_of_rows(dtype):
     for words, n in BORDERS:
         print("words", words, "rows", n, flush=True)
         _check(words, n, torch.bfloat16 if dtype == "bf16" else torch.float32, 3)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_many_rows_on_lines_and_off_them(dtype):
+    """16,384 rows and more whose length is a whole number of 128-byte lines, and not."""
+    import torch
+    for words, pad in ((8447, 1), (8448, 0), (16383, 1), (16384, 0), (16384, 1), (20001, 0), (24575, 1)):
+        print("words", words, "pad", pad, flush=True)
+        _check(words, 16384 + 5, torch.bfloat16 if dtype == "bf16" else torch.float32, pad)
