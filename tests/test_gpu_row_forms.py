@@ -217,3 +217,13 @@ def test_many_rows_on_lines_and_off_them(dtype):
     for words, pad in ((8447, 1), (8448, 0), (16383, 1), (16384, 0), (16384, 1), (20001, 0), (24575, 1)):
         print("words", words, "pad", pad, flush=True)
         _check(words, 16384 + 5, torch.bfloat16 if dtype == "bf16" else torch.float32, pad)
+
+
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_pipelined_form(dtype, pad):
+    """4,096 rows and more: every number of chunks left over when the pipeline's loop ends."""
+    import torch
+    for words in [w for w in FEW if w >= 8192]:
+        print("words", words, flush=True)
+        _check(words, 4096 + 5, torch.bfloat16 if dtype == "bf16" else torch.float32, pad)
