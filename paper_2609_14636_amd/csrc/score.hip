@@ -596,9 +596,9 @@ hipError_t launch_rows_form(const ScoreArgs &a, hipStream_t stream) {
 // 16,200 words, 0.948 and 0.960 at 17,200, 0.953 and 0.965 at 19,800, 0.956 and 0.975 at 20,800; but
 // 0.966 and 0.959 at 12,000, 1.06 and 0.943 at 9,000.  These rows start on 128-byte lines.  Off them
 // eight are ahead, 1.003 and 0.987 at 16,700 words, 1.001 and 0.979 at 19,300: two wavefronts then share a
-// line at each chunk's edge, and may both read it.  fp32 rows hold half the arithmetic per word and leave registers for two such workgroups per CU: sixteen from 8,448 words on,
-// on lines or off them (853 against 869 us at 12,500 words, 30,000 rows; 1.04 of one wavefront's time
-// at 8,192 words, where eight take 1.00).
+// line at each chunk's edge, and may both read it.  fp32 rows hold half the arithmetic per word and leave
+// registers for two such workgroups per CU: sixteen from 8,448 words on, on lines or off them (853 against
+// 869 us at 12,500 words, 30,000 rows; 1.04 of one wavefront's time at 8,192 words, where eight take 1.00).
 template <int DT>
 hipError_t launch_rows(const ScoreArgs &a, hipStream_t stream) {
     const int words = a.vocab / Elem<DT>::kPerVec;
@@ -626,15 +626,21 @@ hipError_t launch_pairs_form(const PairArgs &a, hipStream_t stream) {
 // The form by the row's 16-byte words and the number of tokens, as for single rows.  bf16, eight
 // wavefronts with one chunk in flight for every length -> the form taken here:
 //   words  125, 30,000 tokens: 199 -> 32 us; words 500: 299 -> 78
-//   words 1,500, 30,000 tokens: 383 -> 220 us; words 4,000: 638 -> 564
+//   words 1,000: 16 tokens 7.4 -> 6.9 us, 256 tokens 8.1 -> 7.2, 1,024 tokens 14.7 -> 10.8 (four wavefronts;
+//                one 10.1, 12.5 and 14.0, but 28.7 against 31.6 at 4,096); words 300: 512 tokens 8.7 -> 7.9
+//                (one 8.4), 1,024 tokens 8.4 either way
+//   words 1,500, 30,000 tokens: 383 -> 220 us
+//   words 4,000: 256 tokens 10.9 -> 10.8 us (four wavefronts 11.9), 4,096 tokens 90 -> 89 (93), 40,000 801 -> 771
+//                (790); words 3,100: 4,096 tokens 74 -> 69, but fp32 69.9 -> 69.4 with eight (four 70.2)
 //   words 12,500, 5,000 tokens: 303 -> 298 us (four wavefronts 304)
 //   words 18,992: 64 tokens 23 us either way (four 28), 16,384 tokens 1,434 -> 1,422, 60,000 tokens
 //                 5,210 -> 5,165 (one wavefront per token 5,287)
 template <int DT>
 hipError_t launch_pairs(const PairArgs &a, hipStream_t stream) {
     const int words = a.vocab / Elem<DT>::kPerVec;
-    if (words < 1024) return launch_pairs_form<DT, 1, 4, 2, 1>(a, stream);
-    if (words < 5120) return launch_pairs_form<DT, 4, 1, 4, 1>(a, stream);
+    if (words < 1024 && a.n_rows > (words < 256 ? 256 : 1024))
+        return launch_pairs_form<DT, 1, 4, 2, 1>(a, stream);
+    if (words < (DT == STRIDE_BF16 ? 3584 : 2560)) return launch_pairs_form<DT, 4, 1, 4, 1>(a, stream);
     if (a.n_rows >= 16384) return launch_pairs_form<DT, 4, 1, 4, 2>(a, stream);
     return launch_pairs_form<DT, 8, 1, 4, 1>(a, stream);
 }

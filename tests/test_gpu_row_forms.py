@@ -227,3 +227,13 @@ def test_pipelined_form(dtype, pad):
     for words in [w for w in FEW if w >= 8192]:
         print("words", words, flush=True)
         _check(words, 4096 + 5, torch.bfloat16 if dtype == "bf16" else torch.float32, pad)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_pairs_borders(dtype):
+    """Both sides of the paired form's borders by the number of tokens (256 or 1,024) and the words."""
+    import torch
+    for words, n in ((255, 256), (255, 257), (256, 1024), (256, 1025), (1023, 1024), (1023, 1025), (2559, 24),
+                     (2560, 24), (3583, 24), (3584, 24), (3584, 16384)):
+        print("words", words, "tokens", n, flush=True)
+        _check_pairs(words, n, torch.bfloat16 if dtype == "bf16" else torch.float32, 3)

@@ -10,6 +10,8 @@ CASES = [
     ("rows", 1000, 64, 1500, 1.1),    # one wavefront per row took 1.4 times as long
     ("rows", 1000, 256, 1500, 1.1),
     ("rows", 8200, 64, 8100, 1.06),   # past the border of the pipelined form: 1.11
+    ("pairs", 1000, 64, 1500, 1.1),   # one wavefront per token took 1.3 times as long
+    ("pairs", 1000, 256, 1500, 1.1),  # and here 1.5 times
 ]
 
 
