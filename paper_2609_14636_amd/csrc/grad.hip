@@ -216,18 +216,21 @@ hipError_t launch_grad_form(const GradArgs &a, hipStream_t stream) {
 }
 
 // Wavefronts by the row's 16-byte words: as many as have words for their loads, so that fewer rows
-// are read and written at a time.  Whole call (bits equal), eight wavefronts for every length ->
+// are read and written at a time; and short rows by their number, since few leave the chip idle.  Whole call (bits equal), eight wavefronts for every length ->
 // the form taken here:
 //   words 18,992 (bf16): 64 rows 26.6 -> 21.4 us, 2,000 rows 217 -> 199, 14,000 rows, two thirds of
 //                        them retained, 1,394 -> 1,355, all retained 1,649 -> 1,610
 //   words 25,000 (fp32), 3,000 rows: 448 -> 421 us; words 4,000, 20,000 rows: 391 -> 375
 //   words 500, 20,000 rows: 70.8 -> 53.8 us; words 125, 30,000 rows: 64.1 -> 27.4
-// Sixteen take 198 us against eight's 189 at 2,000 words, eight 105 against four's 95 at 1,000.
+//   words 250: 256 rows 5.7 us either way (one 7.6), 1,024 rows 7.5 -> 7.0 (one 9.0), 4,096 rows 16.8 -> 12.3
+//              (four 13.3); words 64: 256 rows 5.2 either way (one 5.4), 1,024 rows 6.1 -> 5.8 (one 5.6)
+// Sixteen take 198 us against eight's 189 at 2,000 words, eight 105 against four's 95 at 1,000, but four
+// 128 against eight's 120 at 1,030, where the words past four wavefronts' round of 1,024 are a round more.
 template <int DT>
 hipError_t launch_form(const GradArgs &a, hipStream_t stream) {
     const int words = a.vocab / (DT == STRIDE_BF16 ? 8 : 4);
-    if (words < 256) return launch_grad_form<DT, 1, 8>(a, stream);
-    if (words < 1536) return launch_grad_form<DT, 4, 1>(a, stream);
+    if (words < 256 && a.n_rows > (words < 64 ? 256 : 1024)) return launch_grad_form<DT, 1, 8>(a, stream);
+    if (words <= 1024) return launch_grad_form<DT, 4, 1>(a, stream);
     if (words < 3072) return launch_grad_form<DT, 8, 1>(a, stream);
     return launch_grad_form<DT, 16, 1>(a, stream);
 }

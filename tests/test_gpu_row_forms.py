@@ -237,3 +237,37 @@ def test_pairs_borders(dtype):
                      (2560, 24), (3583, 24), (3584, 24), (3584, 16384)):
         print("words", words, "tokens", n, flush=True)
         _check_pairs(words, n, torch.bfloat16 if dtype == "bf16" else torch.float32, 3)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_grad_borders(dtype):
+    """Both sides of the gradient's borders by the number of rows (256 or 1,024), and 1,024 words."""
+    import torch
+    import paper_2609_14636_amd as P
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    per = 8 if dtype == "bf16" else 4
+    for words, n in ((63, 256), (63, 257), (64, 1024), (64, 1025), (255, 1024), (255, 1025), (1024, 40), (1025, 40)):
+        print("words", words, "rows", n, flush=True)
+        vocab = words * per + 3
+        g = torch.Generator(device="cuda").manual_seed(words + n)
+        s = torch.empty((n, (words + 1) * per), dtype=td, device="cuda").normal_(0, 3, generator=g)
+        ids = torch.randint(0, vocab, (n,), dtype=torch.int32, device="cuda", generator=g)
+        ids[0] = vocab - 1
+        lay = P.Layout(torch.tensor([0, 1], dtype=torch.int32, device="cuda"),
+                       torch.tensor([0, n], dtype=torch.int64, device="cuda"), n)
+        path = P.Path(lay, P.STRIDE_UNIT_TOKEN)
+        path.score(vocab, [s], s, ids)
+        path.logp_t.add_(torch.linspace(-1, 1, n, device="cuda"))
+        path.stop_unit.fill_(n - 2)
+        grad = torch.full_like(s, 7.0)
+        path.grad(vocab, s, ids, grad, None, torch.tensor([1], dtype=torch.int32, device="cuda"), scale=0.5)
+        assert int(path.flags.item()) == 0
+        c = 0.5 * (path.logp_t - path.logp_s).double().unsqueeze(1)
+        want = c * s[:, :vocab].double().softmax(1)
+        want[torch.arange(n, device="cuda"), ids.long()] -= c.squeeze(1)
+        want[0] = want[n - 1] = 0
+        got = grad[:, :vocab].double()
+        assert (got[0] == 0).all() and (got[n - 1] == 0).all() and (grad[:, vocab:] == 7.0).all()
+        # one rounding to the logits' type, and fp32's exp2 argument of a logit below 32
+        tol = (2.0 ** -8 if dtype == "bf16" else 4e-6) * want.abs() + 4e-6 * c.abs()
+        assert ((got - want).abs() <= tol).all()

@@ -12,6 +12,9 @@ CASES = [
     ("rows", 8200, 64, 8100, 1.06),   # past the border of the pipelined form: 1.11
     ("pairs", 1000, 64, 1500, 1.1),   # one wavefront per token took 1.3 times as long
     ("pairs", 1000, 256, 1500, 1.1),  # and here 1.5 times
+    ("grad", 250, 256, 400, 1.0),     # one wavefront per row took 1.06 times as long
+    ("grad", 1500, 64, 2000, 1.1),    # four 1.2 times
+    ("grad", 1300, 256, 2000, 1.05),  # four 1.12 times
 ]
 
 
