@@ -59,6 +59,17 @@ __device__ inline void raise_flag(uint32_t *flags, uint32_t bits) {
     if (flags) atomicOr(flags, bits);
 }
 
+// Grid of `blocks` workgroups.  A dimension's threads are counted in 32 bits, and a launch with more runs
+// only what is left of the count, without an error (16,777,216 rows of 16 KiB at four wavefronts each,
+// 275 GB, are one too many): such a grid gets a second dimension, and the kernels number their workgroups
+// by block_index and leave those past the last.  Rows of a multiple of eight workgroups keep their
+// order over the eight XCDs.
+inline dim3 grid_of(int64_t blocks, int threads) {
+    const int64_t row = 0xffffffffll / threads / 8 * 8;
+    return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
+}
+__device__ __forceinline__ int64_t block_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // ---- launchers (one per source file); all asynchronous on `stream` ----
 
 // score.hip

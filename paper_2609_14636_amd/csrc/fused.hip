@@ -85,6 +85,7 @@ struct FusedArgs {
     int32_t n_half;
     int32_t tiles_m, tiles_n;
     int32_t super_rows, super_cols;  // whole super-tiles of 16 x 16 tiles along rows and vocabulary
+    int64_t blocks;        // workgroups that the tiles are numbered over
     int32_t band;          // super-rows per band; a band is walked one super-column at a time
 };
 
@@ -189,7 +190,9 @@ __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
 
     // ---- tile of this workgroup (XCD-aware order) ----
     int tm, tn;
-    tile_of(a, (int)blockIdx.x, tm, tn);
+    const int64_t b = block_index();
+    if (b >= a.blocks) return;
+    tile_of(a, (int)b, tm, tn);
     if (tm >= a.tiles_m || tn >= a.tiles_n) return;
     const int64_t m0 = (int64_t)tm * kBM;
     const int64_t n0 = (int64_t)tn * kBN;
@@ -620,7 +623,7 @@ __global__ __launch_bounds__(kMergeThreads) void fused_merge_kernel(
     __shared__ float s_zy[RW];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int r = threadIdx.x & (RW - 1), sp = threadIdx.x / RW;
-    const int64_t row0 = (int64_t)blockIdx.x * RW, row = row0 + r;
+    const int64_t row0 = block_index() * RW, row = row0 + r;
 #pragma unroll
     for (int q = wave; q < RW; q += kWaves) {
         if (row0 + q >= n_rows) break;
@@ -739,7 +742,7 @@ hipError_t launch_merge(const FusedArgs &a, const int32_t *ids, float *logp_t, u
                         hipStream_t stream) {
     const int rw = a.n_rows < kMergeWide ? 16 : 64;
     hipLaunchKernelGGL(a.n_rows < kMergeWide ? fused_merge_kernel<16> : fused_merge_kernel<64>,
-                       dim3((unsigned)((a.n_rows + rw - 1) / rw)), dim3(kMergeThreads), 0, stream,
+                       grid_of((a.n_rows + rw - 1) / rw, kMergeThreads), dim3(kMergeThreads), 0, stream,
                        a.partial, a.h, a.w, ids, logp_t, a.n_rows, a.n_half, a.vocab, a.d, flags);
     return hipGetLastError();
 }
@@ -807,19 +810,20 @@ hipError_t launch_fused_teacher(const uint16_t *h, const uint16_t *w, const int3
         a.tiles_n = (vocab + 32 * nb - 1) / (32 * nb);
         a.super_cols = a.tiles_n / 16;
         a.n_half = a.tiles_n;  // one partial per tile, at most one per 128 entries
+        a.blocks = 8 * ((a.tiles_n + 7) / 8);
         hipLaunchKernelGGL(nb == 8 ? fused_row8_kernel : (nb == 7 ? fused_row7_kernel
                                                                  : (nb == 6 ? fused_row6_kernel : fused_row4_kernel)),
-                           dim3((unsigned)(8 * ((a.tiles_n + 7) / 8))), dim3(kThreads), kLdsBytes, stream, a);
+                           grid_of(a.blocks, kThreads), dim3(kThreads), kLdsBytes, stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_merge(a, ids, logp_t, flags, stream);
     }
     const int64_t rem = a.tiles_m - a.super_rows * 16;
-    const int64_t blocks = 8 * ((int64_t)a.super_rows * a.super_cols * 32 +
-                                (int64_t)a.super_rows * 2 * (a.tiles_n - a.super_cols * 16) +
-                                rem * ((a.tiles_n + 7) / 8));
-    if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;  // grid past the 32-bit limit
-    hipLaunchKernelGGL(fused_lse_kernel, dim3((unsigned)blocks), dim3(kThreads), kLdsBytes, stream, a);
+    a.blocks = 8 * ((int64_t)a.super_rows * a.super_cols * 32 +
+                    (int64_t)a.super_rows * 2 * (a.tiles_n - a.super_cols * 16) +
+                    rem * ((a.tiles_n + 7) / 8));
+    if (a.blocks > 0x7fffffff) return hipErrorInvalidConfiguration;  // past tile_of's 32-bit numbers
+    hipLaunchKernelGGL(fused_lse_kernel, grid_of(a.blocks, kThreads), dim3(kThreads), kLdsBytes, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_merge(a, ids, logp_t, flags, stream);

@@ -212,8 +212,8 @@ __global__ __launch_bounds__(256) void restart_waves_kernel(RestartArgs a, int h
     __shared__ int32_t s_long[256];
     const int64_t R = a.L.n_rollouts;
     const int tid = threadIdx.x;
-    if ((int)blockIdx.x >= helpers) {
-        const int64_t r = (int64_t)((int)blockIdx.x - helpers) * kWaves +
+    if (block_index() >= helpers) {
+        const int64_t r = (block_index() - helpers) * kWaves +
                           __builtin_amdgcn_readfirstlane(tid / kWave);
         if (r >= R) return;
         const Record rec = record_of(a, r, tid % kWave == 0);
@@ -248,21 +248,23 @@ template <typename VT, int NT>
 __global__ __launch_bounds__(NT) void restart_block_kernel(RestartArgs a) {
     __shared__ int64_t s_min, s_idx[NT / kWave];
     __shared__ double s_val[NT / kWave];
-    const Record rec = record_of(a, blockIdx.x, threadIdx.x == 0);
-    if (rec.len >= 0) pick<VT, NT, 8>(a, blockIdx.x, rec, threadIdx.x, &s_min, s_val, s_idx);
+    const int64_t r = block_index();
+    if (r >= a.L.n_rollouts) return;
+    const Record rec = record_of(a, r, threadIdx.x == 0);
+    if (rec.len >= 0) pick<VT, NT, 8>(a, r, rec, threadIdx.x, &s_min, s_val, s_idx);
 }
 
 template <typename VT>
-void launch_restart_groups(const RestartArgs &a, unsigned R, int64_t n_units, hipStream_t stream) {
+void launch_restart_groups(const RestartArgs &a, int64_t R, int64_t n_units, hipStream_t stream) {
     const int64_t per = n_units / R;
     if (per <= 128) {
         // no record is longer than the call
-        const int helpers = n_units <= kWaveLength ? 0 : (R < (unsigned)kHelpers ? (int)R : kHelpers);
-        hipLaunchKernelGGL(restart_waves_kernel<VT>, dim3((R + 3) / 4 + helpers), dim3(256), 0, stream, a, helpers);
+        const int helpers = n_units <= kWaveLength ? 0 : (R < kHelpers ? (int)R : kHelpers);
+        hipLaunchKernelGGL(restart_waves_kernel<VT>, grid_of((R + 3) / 4 + helpers, 256), dim3(256), 0, stream, a, helpers);
     } else if (per <= 1024)
-        hipLaunchKernelGGL((restart_block_kernel<VT, 256>), dim3(R), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((restart_block_kernel<VT, 256>), grid_of(R, 256), dim3(256), 0, stream, a);
     else
-        hipLaunchKernelGGL((restart_block_kernel<VT, 512>), dim3(R), dim3(512), 0, stream, a);
+        hipLaunchKernelGGL((restart_block_kernel<VT, 512>), grid_of(R, 512), dim3(512), 0, stream, a);
 }
 
 }  // namespace
@@ -285,7 +287,7 @@ hipError_t launch_restart(const stride_layout &L, int32_t unit, const void *valu
     a.k_max = k_max;
     a.flags = flags;
     const int64_t n_units = unit == STRIDE_UNIT_TURN ? L.n_turns : L.n_tokens;
-    const unsigned R = (unsigned)L.n_rollouts;
+    const int64_t R = L.n_rollouts;
     if (unit == STRIDE_UNIT_TURN)
         launch_restart_groups<double>(a, R, n_units, stream);
     else

@@ -771,7 +771,7 @@ __global__ __launch_bounds__(256) void stop_step_kernel(int32_t n_active, const 
                                                         int32_t *state_units, int32_t *stop_unit,
                                                         uint32_t *flags) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t a = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
+    const int64_t a = block_index() * (blockDim.x / kWave) + (threadIdx.x / kWave);
     if (a >= n_active) return;
     const int32_t slot = rid[a];
     if (slot < 0) {
@@ -830,13 +830,13 @@ hipError_t launch_stop_step(int32_t n_active, const int32_t *rid, const int64_t 
                             int32_t *state_units, int32_t *stop_unit, uint32_t *flags,
                             hipStream_t stream) {
     if (n_active == 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((n_active + 3) / 4);
+    const dim3 grid = grid_of(((int64_t)n_active + 3) / 4, 256);
     if (unit == STRIDE_UNIT_TURN)
-        hipLaunchKernelGGL(stop_step_kernel<double>, dim3(blocks), dim3(256), 0, stream, n_active,
+        hipLaunchKernelGGL(stop_step_kernel<double>, grid, dim3(256), 0, stream, n_active,
                            rid, new_off, static_cast<const double *>(values), domain, lambda, n_dom,
                            state_cum, state_units, stop_unit, flags);
     else
-        hipLaunchKernelGGL(stop_step_kernel<float>, dim3(blocks), dim3(256), 0, stream, n_active,
+        hipLaunchKernelGGL(stop_step_kernel<float>, grid, dim3(256), 0, stream, n_active,
                            rid, new_off, static_cast<const float *>(values), domain, lambda, n_dom,
                            state_cum, state_units, stop_unit, flags);
     return hipGetLastError();

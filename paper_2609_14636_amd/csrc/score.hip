@@ -161,10 +161,10 @@ __global__ __launch_bounds__(W *RW *kWave) void score_rows_kernel(ScoreArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wave = W == 1 ? 0 : wid;
-    const int64_t item = (int64_t)blockIdx.x * RW + (W == 1 ? wid : 0);
+    const int64_t item = block_index() * RW + (W == 1 ? wid : 0);
     const bool two = a.student != nullptr;
     const int64_t n_items = two ? 2 * a.n_rows : a.n_rows;
-    if (item >= n_items) return;  // W > 1: never, the grid has exactly n_items workgroups
+    if (item >= n_items) return;  // W > 1: the whole workgroup, before any barrier
     const bool is_student = two && (item & 1);
     const int64_t row = two ? (item >> 1) : item;
     float *out = is_student ? a.logp_s : a.logp_t;
@@ -391,8 +391,8 @@ __global__ __launch_bounds__(W *RW *kWave) void score_pairs_kernel(PairArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wave = W == 1 ? 0 : wid;
-    const int64_t row = (int64_t)blockIdx.x * RW + (W == 1 ? wid : 0);
-    if (row >= a.n_rows) return;  // W > 1: never, the grid has exactly n_rows workgroups
+    const int64_t row = block_index() * RW + (W == 1 ? wid : 0);
+    if (row >= a.n_rows) return;  // W > 1: the whole workgroup, before any barrier
     const int d = a.row_dom ? (int)a.row_dom[row] : 0;
     if (d >= a.n_teachers) {  // the same for the token's wavefronts: they leave before any barrier
         if (wave == 0 && lane == 0) {
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(W *RW *kWave) void score_pairs_kernel(PairArgs a) {
 // kBadDomain and raise a flag, so the scoring kernel writes NaN for them.
 __global__ __launch_bounds__(256) void row_domain_kernel(stride_layout L, int32_t n_teachers,
                                                          uint8_t *row_dom, uint32_t *flags) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = block_index() * blockDim.x + threadIdx.x;
     if (i >= L.n_tokens) return;
     // last turn t with turn_tok_off[t] <= i
     int64_t lo = 0, hi = L.n_turns;  // answer in [0, T)
@@ -570,7 +570,7 @@ __global__ __launch_bounds__(256) void row_domain_kernel(stride_layout L, int32_
 template <int DT, int W, int RW, int U, int D>
 hipError_t launch_rows_form(const ScoreArgs &a, hipStream_t stream) {
     const int64_t items = a.student ? 2 * a.n_rows : a.n_rows;
-    hipLaunchKernelGGL((score_rows_kernel<DT, W, RW, U, D>), dim3((unsigned)((items + RW - 1) / RW)),
+    hipLaunchKernelGGL((score_rows_kernel<DT, W, RW, U, D>), grid_of((items + RW - 1) / RW, W * RW * kWave),
                        dim3(W * RW * kWave), 0, stream, a);
     return hipGetLastError();
 }
@@ -618,7 +618,7 @@ hipError_t launch_rows(const ScoreArgs &a, hipStream_t stream) {
 
 template <int DT, int W, int RW, int U, int D>
 hipError_t launch_pairs_form(const PairArgs &a, hipStream_t stream) {
-    hipLaunchKernelGGL((score_pairs_kernel<DT, W, RW, U, D>), dim3((unsigned)((a.n_rows + RW - 1) / RW)),
+    hipLaunchKernelGGL((score_pairs_kernel<DT, W, RW, U, D>), grid_of((a.n_rows + RW - 1) / RW, W * RW * kWave),
                        dim3(W * RW * kWave), 0, stream, a);
     return hipGetLastError();
 }
@@ -673,7 +673,7 @@ hipError_t launch_row_domain(const stride_layout &L, int32_t n_teachers, uint8_t
                              uint32_t *flags, hipStream_t stream) {
     if (L.n_tokens == 0) return hipSuccess;
     const int64_t blocks = (L.n_tokens + 255) / 256;
-    hipLaunchKernelGGL(row_domain_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, L,
+    hipLaunchKernelGGL(row_domain_kernel, grid_of(blocks, 256), dim3(256), 0, stream, L,
                        n_teachers, row_dom, flags);
     return hipGetLastError();
 }

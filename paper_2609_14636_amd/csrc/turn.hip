@@ -22,7 +22,8 @@ __global__ __launch_bounds__(256) void turn_mean_kernel(stride_layout L,
                                                         float *__restrict__ kl,
                                                         double *turn_mean, uint32_t *flags) {
     __shared__ double part[256 / kWave];
-    const int64_t t = blockIdx.x;
+    const int64_t t = block_index();
+    if (t >= L.n_turns) return;
     const int64_t a = L.turn_tok_off[t], b = L.turn_tok_off[t + 1];
     const bool bad = a < 0 || b > L.n_tokens || b < a || (t == 0 && a != 0) ||
                      (t == L.n_turns - 1 && b != L.n_tokens);
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(256) void turn_mean_kernel(stride_layout L,
 hipError_t launch_turn_mean(const stride_layout &L, const float *logp_t, const float *logp_s,
                             float *kl, double *turn_mean, uint32_t *flags, hipStream_t stream) {
     if (L.n_turns == 0) return hipSuccess;
-    hipLaunchKernelGGL(turn_mean_kernel, dim3((unsigned)L.n_turns), dim3(256), 0, stream, L, logp_t,
+    hipLaunchKernelGGL(turn_mean_kernel, grid_of(L.n_turns, 256), dim3(256), 0, stream, L, logp_t,
                        logp_s, kl, turn_mean, flags);
     return hipGetLastError();
 }
