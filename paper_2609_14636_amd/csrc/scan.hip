@@ -302,9 +302,9 @@ __global__ __launch_bounds__(kScanThreads) void stop_scan_kernel(StopArgs a) {
         double v = 0.0;
         bool h = false;
         int64_t rj = -1;  // rollout holding unit u, -1 if none (only with bad offsets)
-        if (u < a.n_units && r >= 0) {
-            while (r + 1 < R && off(r + 1) <= u) ++r;
-            const int64_t first = off(r), n = off(r + 1) - first, local = u - first;
+        if (u < a.n_units) {
+            while (r + 1 < R && off(r + 1) <= u) ++r;  // from -1 on where the first rollout starts late
+            const int64_t first = r >= 0 ? off(r) : 0, n = r >= 0 ? off(r + 1) - first : 0, local = u - first;
             if (local >= 0 && local < n) {
                 const int64_t k0 = r - rb < kCap ? s_k0[r - rb] : prefix(r, n);
                 h = (local == 0);

@@ -91,6 +91,36 @@ def test_units_in_no_rollout():
     assert c[3:9].tolist() == [-1, -2, -1, -2, -3, -4] and stop.tolist() == [-1, 2]
 
 
+@pytest.mark.parametrize("late,early", [(3, 0), (0, 5), (5000, 7000), (2047, 2049)])
+def test_units_in_no_rollout_as_tiles(late, early):
+    """The same with more rollouts than the groups take: the tile scan.  The units before the first
+    rollout and past the last one are NaN, whole tiles of them too; the others are summed as without them."""
+    import torch
+    import paper_2609_14636_amd as P
+    R = (1 << 15) + 1
+    g = np.random.default_rng(late + early)
+    off = late + np.concatenate([[0], np.cumsum(g.integers(0, 3, R))]).astype(np.int64)
+    U = int(off[-1]) + early
+    vals = -np.abs(g.normal(0.5, 0.5, U))
+    rows = np.arange(U + 1, dtype=np.int64)
+    inner = slice(late, U - early)
+    cum_o, stop_o, ret_o = H.OP.O.stop(off - late, vals[inner].copy(), np.full(R, -1.2), np.zeros(R, np.int32),
+                                       np.arange(U - late - early + 1, dtype=np.int64))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    lay = P.Layout(dev(off.astype(np.int32)), dev(rows), U)
+    cum = torch.full((U + 5,), 5.0, dtype=torch.float64, device="cuda")
+    stop = torch.full((R,), 77, dtype=torch.int32, device="cuda")
+    ret = torch.full((R,), 77, dtype=torch.int64, device="cuda")
+    flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(P.stride_workspace_size(lay, P.STRIDE_UNIT_TURN), dtype=torch.uint8, device="cuda")
+    P.stride_stop(lay, P.STRIDE_UNIT_TURN, dev(vals), [-1.2], None, cum, stop, ret, flags, ws)
+    assert int(flags.item()) == P.STRIDE_FLAG_BAD_OFFSETS
+    c = cum.cpu().numpy()
+    assert np.isnan(c[:late]).all() and np.isnan(c[U - early:U]).all() and (c[U:] == 5.0).all()
+    assert np.max(np.abs(c[inner] - cum_o)) <= 1e-12
+    assert np.array_equal(stop.cpu().numpy(), stop_o) and np.array_equal(ret.cpu().numpy(), ret_o)
+
+
 def test_many_short_rollouts_as_tiles():
     """One rollout more than the groups take: the tile scan, against float64 sums."""
     import torch
