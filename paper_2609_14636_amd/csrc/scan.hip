@@ -303,7 +303,23 @@ __global__ __launch_bounds__(kScanThreads) void stop_scan_kernel(StopArgs a) {
         bool h = false;
         int64_t rj = -1;  // rollout holding unit u, -1 if none (only with bad offsets)
         if (u < a.n_units) {
-            while (r + 1 < R && off(r + 1) <= u) ++r;  // from -1 on where the first rollout starts late
+            // on to the last rollout that starts at or before u (from -1 on where the first starts late),
+            // in steps that double, since most of the rollouts on the way can be empty
+            if (r + 1 < R && off(r + 1) <= u) {
+                int64_t next = R;
+                ++r;
+                for (int64_t step = 1; r + step < R; step <<= 1) {
+                    if (off(r + step) > u) {
+                        next = r + step;
+                        break;
+                    }
+                    r += step;
+                }
+                while (next - r > 1) {
+                    const int64_t mid = (r + next) >> 1;
+                    if (off(mid) <= u) r = mid; else next = mid;
+                }
+            }
             const int64_t first = r >= 0 ? off(r) : 0, n = r >= 0 ? off(r + 1) - first : 0, local = u - first;
             if (local >= 0 && local < n) {
                 const int64_t k0 = r - rb < kCap ? s_k0[r - rb] : prefix(r, n);
