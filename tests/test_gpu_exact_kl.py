@@ -57,8 +57,8 @@ def test_exact_kl_parity(name, scale):
 
 
 def test_exact_kl_on_the_one_wavefront_kernel():
-    """65,600 tokens (the paired pass shares rows among eight wavefronts only below 65,536), with a
-    ragged vocabulary of 1,001 entries: the exact KL and both log-probabilities of every token
+    """65,600 tokens (the paired pass shares rows of this length among four wavefronts only up to 256),
+    with a ragged vocabulary of 1,001 entries: the exact KL and both log-probabilities of every token
     against the oracle."""
     wl = W.make("reasoning", seed=13, scale=dict(R=4, tok=16400, vocab=1001))
     assert wl.n_tokens >= 65536

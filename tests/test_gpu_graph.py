@@ -126,11 +126,13 @@ def test_graph_replay_fused_equals_eager():
     say("[graph fused] 3 replays equal to eager")
 
 
-def test_graph_replay_of_the_allocation_free_stop_test():
+@pytest.mark.parametrize("tiles", [False, True])
+def test_graph_replay_of_the_allocation_free_stop_test(tiles):
     """stride_stop_noalloc, the entry point for callers that cannot allocate, captured in a HIP
     graph: every replay equals stride_stop with a caller workspace on the same inputs bit for bit,
-    with eager calls between the replays that leave other contents in the shared fixed scratch
-    (a smaller layout through stride_stop_noalloc itself) and the values changed in place."""
+    with eager calls of a smaller layout between the replays and the values changed in place.  With
+    tiles both layouts are past what a group of threads takes for each rollout, so that the eager calls
+    leave other contents in the shared fixed scratch."""
     import torch
     import paper_2609_14636_amd as P
 
@@ -144,16 +146,18 @@ def test_graph_replay_of_the_allocation_free_stop_test():
         tto[1:] = np.cumsum(sizes)
         return rto, tto
 
-    sizes = np.concatenate([g.integers(1, 3000, size=40), [70000, 2048, 2049]])
+    sizes = np.concatenate([g.integers(1, 3000, size=40), [70000, 2048, 2049],
+                            [450000] if tiles else []]).astype(np.int64)
     rto, tto = layout(sizes)
     N, R = int(tto[-1]), sizes.size
+    assert (N > 1 << 19) == tiles
     dom = g.integers(0, 2, size=R).astype(np.int32)
     lay = P.Layout(dev(rto), dev(tto), N, dev(dom))
     vals = dev((-np.abs(g.normal(0.5, 0.5, size=N))).astype(np.float32))
     start = dev((g.random(R) * sizes * 0.3).astype(np.int32))
     lam = [-150.0, -900.0]
-    # a second, smaller layout whose eager calls overwrite the fixed scratch between replays
-    sizes2 = g.integers(1, 5000, size=9)
+    # a second, smaller layout for eager calls between replays
+    sizes2 = np.array([40000, 50000, 30001]) if tiles else g.integers(1, 5000, size=9)
     rto2, tto2 = layout(sizes2)
     lay2 = P.Layout(dev(rto2), dev(tto2), int(tto2[-1]), None)
     vals2 = dev((-np.abs(g.normal(0.3, 0.2, size=int(tto2[-1])))).astype(np.float32))

@@ -149,7 +149,7 @@ def test_small_vocab_ragged_parity(vocab, dtype):
 @pytest.mark.parametrize("dtype", [W.BF16, W.F32])
 def test_small_vocab_on_the_one_wavefront_kernel(vocab, dtype):
     """The small vocabularies above again, in a batch of 8,400 rows (16,800 row items), so the
-    one-wavefront kernel's tail handling (a row shorter than one 16-byte word, or one word and a
+    one-wavefront form's tail handling (a row shorter than one 16-byte word, or one word and a
     ragged tail) is compared with the oracle too."""
     g = np.random.default_rng(vocab * 100 + dtype)
     lengths = [g.integers(200, 500, size=3) for _ in range(7)]
@@ -220,8 +220,8 @@ def test_random_small_layouts():
 @pytest.mark.parametrize("pad", [0, 8200])
 def test_data_error_flags(pad):
     """Non-finite rows and token ids out of range give NaN and flags; with pad, a third rollout of
-    valid rows lifts the batch past 16,384 row items, so the one-wavefront kernel handles the same
-    bad rows that the shared-row kernel handles without it."""
+    valid rows lifts the batch past 1,024 row items, so the one-wavefront form handles the same
+    bad rows that four wavefronts share without it."""
     import torch
     import paper_2609_14636_amd as P
     vocab = 64
@@ -258,7 +258,7 @@ def test_data_error_flags(pad):
 @pytest.mark.parametrize("pad", [0, 8200])
 def test_empty_turn_and_bad_domain_flags(pad):
     """An empty turn and a rollout routed to a teacher that does not exist; with pad, a third
-    rollout of valid rows moves the batch onto the one-wavefront kernel."""
+    rollout of valid rows moves the batch onto the one-wavefront form."""
     import torch
     import paper_2609_14636_amd as P
     rto = torch.tensor([0, 2, 3] + ([4] if pad else []), dtype=torch.int32, device="cuda")
@@ -376,28 +376,27 @@ def test_stop_and_restart_a_million_short_rollouts():
     assert 0 < int((s >= 0).sum()) < s.size
 
 
-@pytest.mark.parametrize("n_rows,with_student", [(8191, True), (8192, True), (16383, False),
-                                                  (16384, False)])
+@pytest.mark.parametrize("n_rows,with_student", [(1024, True), (1025, True), (2048, False), (2049, False),
+                                                  (8191, True), (8192, True), (16383, False), (16384, False)])
 def test_either_side_of_the_shared_row_threshold(n_rows, with_student):
-    """Batches of fewer than 16,384 row items (teacher plus student rows) share each row among the
-    eight wavefronts of a workgroup; larger ones take one wavefront per row.  Both sides of the
+    """Batches of up to 2,048 row items (teacher plus student rows) of this length, 512 words, share each row
+    among the four wavefronts of a workgroup; larger ones take one wavefront per row.  Both sides of the
     threshold against the oracle on every row, and the shared form run twice is bit-identical."""
     wl = W.make("reasoning", seed=17, scale=dict(R=1, tok=n_rows, vocab=4099))
     gpu, _, lam, alpha, _ = _parity(wl, with_student=with_student)
     items = n_rows * (2 if with_student else 1)
-    if items < 16384:
+    if items <= 2048:
         again = H.run_gpu(wl, lam, alpha, with_student=with_student)
         for k in ("logp_t", "logp_s", "kl", "turn_mean", "cum", "stop_unit", "k_star"):
             if gpu.get(k) is not None:
                 assert np.array_equal(gpu[k].view(np.uint8), again[k].view(np.uint8)), k
 
 
-@pytest.mark.parametrize("tok", [500, 1100])
-def test_fp32_rows_either_side_of_the_shared_row_threshold(tok):
+@pytest.mark.parametrize("tok,seed", [(60, 24), (500, 23), (1100, 23)])
+def test_fp32_rows_either_side_of_the_shared_row_threshold(tok, seed):
     """fp32 logits (the tiny workload's generator, V = 1024) with 2 rollouts x 4 turns x tok
-    tokens: 8,000 row items run the shared-row kernel, 17,600 the one-wavefront kernel; every
-    row against the oracle."""
-    wl = W.make("tiny", seed=23, scale=dict(R=2, turns=4, tok=tok))
+    tokens: 960 row items run four wavefronts each, 8,000 and 17,600 one; every row against the oracle."""
+    wl = W.make("tiny", seed=seed, scale=dict(R=2, turns=4, tok=tok))
     assert wl.dtype == W.F32
     _parity(wl)
 
