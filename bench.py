@@ -844,7 +844,8 @@ def main():
         kept = int(out["retained"].sum())
         gbytes = kept * 2 * wl.vocab * wl.esize + (n_tok - kept) * wl.vocab * wl.esize + 13 * n_tok
         # read+write reference on the same rows: retained rows copied from the student logits,
-        # the others zero-filled without a read, one wavefront per row (the gradient's pattern)
+        # the others zero-filled without a read, eight wavefronts per row (the gradient's loads and
+        # stores; it has up to sixteen)
         rmask = torch.from_numpy(retained_row_mask(wl, out["stop_unit"], wl.start)).cuda()
         assert int(rmask.sum().item()) == kept
         row_bytes = (wl.vocab * wl.esize) // 16 * 16

@@ -62,7 +62,9 @@ enum { STRIDE_UNIT_TURN = 0, STRIDE_UNIT_TOKEN = 1 };
 enum {
     STRIDE_FLAG_TOKEN_OOB = 1,   /* token id outside [0, vocab): that row's outputs are NaN        */
     STRIDE_FLAG_EMPTY_TURN = 2,  /* a turn with no rows: its mean is NaN                            */
-    STRIDE_FLAG_BAD_OFFSETS = 4, /* offsets not monotone, not starting at 0 or not ending at N/T    */
+    STRIDE_FLAG_BAD_OFFSETS = 4, /* offsets not monotone, not starting at 0 or not ending at N/T:
+                                    units in no turn or rollout give NaN; where spans overlap, the
+                                    values of the units in both are those of either              */
     STRIDE_FLAG_NONFINITE = 8,   /* a row holds NaN or +inf, or only -inf: its outputs are NaN      */
     STRIDE_FLAG_BAD_DOMAIN = 16, /* domain[r] outside [0, n_dom), or [0, n_teachers) when routing  */
     STRIDE_FLAG_SPIN_LIMIT = 32  /* a cross-workgroup wait gave up; the scan results are not valid  */
@@ -123,8 +125,9 @@ size_t stride_workspace_size(const stride_layout *layout, int32_t unit);
  *
  * Values: -inf logits carry no mass; NaN, +inf or an all -inf row raise
  * STRIDE_FLAG_NONFINITE and give NaN outputs for that row.  Finite logits are
- * supported up to |x| = 2^127 (the exponent is formed as x * log2(e) in fp32);
- * rows with larger finite values are outside the supported range.
+ * supported up to |x| = 2^127 (the exponent is formed as x * log2(e) in fp32), and
+ * entries below -2^127, such as masks of the type's lowest value, carry no mass beside
+ * a larger one; rows with larger finite values are outside the supported range.
  */
 stride_status stride_score(const stride_layout *layout, int32_t vocab, int64_t ld, int32_t dtype,
                            int32_t n_teachers, const void *const *teacher_logits,
@@ -350,7 +353,7 @@ stride_status stride_probe_copy(const void *src, void *dst, const uint8_t *row_m
  *
  * In the library built for testing (libstride_debug.so, scan compiled with
  * STRIDE_SCAN_DELAY_HOOK), later stride_stop / stride_stop_noalloc calls that scan tiles (more
- * than 2^19 units, 2^15 per rollout on average or 2^15 rollouts) make those
+ * than 2^19 units, 2^15 per rollout on average or 2^15 rollouts) make the tiles
  * picked by a hash of (seed, tile) -- about one in `one_in` -- sleep 1 .. `sleeps` times
  * s_sleep(127) (about 8,000 cycles each) before publishing their aggregate, so that their
  * successors look back over descriptors that are not yet published.  The waits stay far below

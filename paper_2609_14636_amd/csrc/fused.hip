@@ -412,8 +412,10 @@ __global__ __launch_bounds__(kThreads, 1) void fused_row4_kernel(FusedArgs a) { 
 // registers as MFMA A operands, since no two waves share a row of it, and H through a ring of
 // kRing LDS buffers of one 64-wide K stage.  The loads of stage t + 3 are issued when stage t
 // begins, so W has three stages to arrive (the tile kernel's window is one and a half, short of
-// HBM's latency), and the stages run on across the passes over a workgroup's share, so the ring
-// never drains.  A workgroup's K stages start at its own place, so that the chip's W reads, all
+// HBM's latency), and the stages run on across the passes over a workgroup's share.  At the end of a
+// pass, though, a wave reads its running (max, sum) from LDS, and such a read waits for all loads into LDS
+// that are in flight, so all but the newest stage's W lands first, once for each of the three passes at
+// V = 151,936.  A workgroup's K stages start at its own place, so that the chip's W reads, all
 // rows at the same column otherwise, spread over the memory channels.  Per token a wave keeps its
 // (max, sum) over its passes in LDS; the workgroup writes one partial per token.
 constexpr int kRing = 4;
@@ -782,7 +784,7 @@ hipError_t launch_fused_teacher(const uint16_t *h, const uint16_t *w, const int3
     if (e != hipSuccess) return e;
     if (n_rows <= kMaxRowsN) {
         // no more workgroups than partials that the workspace holds; a share's bytes fit the 32-bit
-        // range of one descriptor
+        // range of one descriptor (W of 545 GB and more, host memory that the GPU reads, goes to the tiles)
         const int grid = a.n_half < kCUs ? a.n_half : kCUs;
         if (((int64_t)vocab / grid + 2 * kShareRows) * d * 2 < 0x7f000000) {
             a.n_half = grid;

@@ -22,7 +22,8 @@
 //      associated in the same order on every run: cum is bit-reproducible.
 //   5. The first crossing per rollout is an integer min, reduced in LDS and
 //      then with one global atomicMin per rollout per tile.
-// A call of one tile needs none of this and runs as one workgroup in one launch.
+// Calls of up to 2^19 units, 2^15 rollouts and 2^15 units for each on average need none of this: a group
+// of threads takes each rollout, in one launch (stop_waves_kernel, stop_block_kernel).
 // Waits are bounded: past the spin limit the tile gives up, raises
 // STRIDE_FLAG_SPIN_LIMIT and writes NaN, so no wave can hang.
 #include <atomic>
