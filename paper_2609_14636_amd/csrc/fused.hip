@@ -190,7 +190,7 @@ __device__ __forceinline__ void fused_lse(const FusedArgs &a) {
 
     // ---- tile of this workgroup (XCD-aware order) ----
     int tm, tn;
-    const int64_t b = block_index();
+    const int64_t b = block_index<kThreads>();
     if (b >= a.blocks) return;
     tile_of(a, (int)b, tm, tn);
     if (tm >= a.tiles_m || tn >= a.tiles_n) return;
@@ -625,7 +625,7 @@ __global__ __launch_bounds__(kMergeThreads) void fused_merge_kernel(
     __shared__ float s_zy[RW];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int r = threadIdx.x & (RW - 1), sp = threadIdx.x / RW;
-    const int64_t row0 = block_index() * RW, row = row0 + r;
+    const int64_t row0 = block_index<kMergeThreads>() * RW, row = row0 + r;
 #pragma unroll
     for (int q = wave; q < RW; q += kWaves) {
         if (row0 + q >= n_rows) break;

@@ -32,7 +32,7 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
 __global__ __launch_bounds__(256) void grad_mask_kernel(stride_layout L, int32_t unit,
                                                         const int32_t *start, const int32_t *stop,
                                                         uint8_t *mask, uint32_t *flags) {
-    const int64_t i = block_index() * blockDim.x + threadIdx.x;
+    const int64_t i = block_index<256>() * blockDim.x + threadIdx.x;
     if (i >= L.n_tokens) return;
     uint8_t m = 0;
     if (L.n_turns > 0 && L.turn_tok_off[0] <= i) {
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(W *RW *kWave) void opd_grad_kernel(GradArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int sub = W == 1 ? 0 : wid;  // this wavefront's share of the row
-    const int64_t row = block_index() * RW + (W == 1 ? wid : 0);
+    const int64_t row = block_index<W * RW * kWave>() * RW + (W == 1 ? wid : 0);
     if (row >= a.n_rows) return;
     const size_t off = (size_t)row * a.ld * ES;
     const u32x4 *src = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.student) + off);

@@ -212,8 +212,8 @@ __global__ __launch_bounds__(256) void restart_waves_kernel(RestartArgs a, int h
     __shared__ int32_t s_long[256];
     const int64_t R = a.L.n_rollouts;
     const int tid = threadIdx.x;
-    if (block_index() >= helpers) {
-        const int64_t r = (block_index() - helpers) * kWaves +
+    if (block_index<256>() >= helpers) {
+        const int64_t r = (block_index<256>() - helpers) * kWaves +
                           __builtin_amdgcn_readfirstlane(tid / kWave);
         if (r >= R) return;
         const Record rec = record_of(a, r, tid % kWave == 0);
@@ -248,7 +248,7 @@ template <typename VT, int NT>
 __global__ __launch_bounds__(NT) void restart_block_kernel(RestartArgs a) {
     __shared__ int64_t s_min, s_idx[NT / kWave];
     __shared__ double s_val[NT / kWave];
-    const int64_t r = block_index();
+    const int64_t r = block_index<NT>();
     if (r >= a.L.n_rollouts) return;
     const Record rec = record_of(a, r, threadIdx.x == 0);
     if (rec.len >= 0) pick<VT, NT, 8>(a, r, rec, threadIdx.x, &s_min, s_val, s_idx);

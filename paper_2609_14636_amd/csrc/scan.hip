@@ -788,7 +788,7 @@ __global__ __launch_bounds__(256) void stop_step_kernel(int32_t n_active, const 
                                                         int32_t *state_units, int32_t *stop_unit,
                                                         uint32_t *flags) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t a = block_index() * (blockDim.x / kWave) + (threadIdx.x / kWave);
+    const int64_t a = block_index<256>() * (blockDim.x / kWave) + (threadIdx.x / kWave);
     if (a >= n_active) return;
     const int32_t slot = rid[a];
     if (slot < 0) {

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(W *RW *kWave) void score_rows_kernel(ScoreArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wave = W == 1 ? 0 : wid;
-    const int64_t item = block_index() * RW + (W == 1 ? wid : 0);
+    const int64_t item = block_index<W * RW * kWave>() * RW + (W == 1 ? wid : 0);
     const bool two = a.student != nullptr;
     const int64_t n_items = two ? 2 * a.n_rows : a.n_rows;
     if (item >= n_items) return;  // W > 1: the whole workgroup, before any barrier
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(W *RW *kWave) void score_pairs_kernel(PairArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wave = W == 1 ? 0 : wid;
-    const int64_t row = block_index() * RW + (W == 1 ? wid : 0);
+    const int64_t row = block_index<W * RW * kWave>() * RW + (W == 1 ? wid : 0);
     if (row >= a.n_rows) return;  // W > 1: the whole workgroup, before any barrier
     const int d = a.row_dom ? (int)a.row_dom[row] : 0;
     if (d >= a.n_teachers) {  // the same for the token's wavefronts: they leave before any barrier
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(W *RW *kWave) void score_pairs_kernel(PairArgs a) {
 // kBadDomain and raise a flag, so the scoring kernel writes NaN for them.
 __global__ __launch_bounds__(256) void row_domain_kernel(stride_layout L, int32_t n_teachers,
                                                          uint8_t *row_dom, uint32_t *flags) {
-    const int64_t i = block_index() * blockDim.x + threadIdx.x;
+    const int64_t i = block_index<256>() * blockDim.x + threadIdx.x;
     if (i >= L.n_tokens) return;
     // last turn t with turn_tok_off[t] <= i
     int64_t lo = 0, hi = L.n_turns;  // answer in [0, T)

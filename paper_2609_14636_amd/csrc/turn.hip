@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) void turn_mean_kernel(stride_layout L,
                                                         float *__restrict__ kl,
                                                         double *turn_mean, uint32_t *flags) {
     __shared__ double part[256 / kWave];
-    const int64_t t = block_index();
+    const int64_t t = block_index<256>();
     if (t >= L.n_turns) return;
     const int64_t a = L.turn_tok_off[t], b = L.turn_tok_off[t + 1];
     const bool bad = a < 0 || b > L.n_tokens || b < a || (t == 0 && a != 0) ||
