@@ -587,7 +587,11 @@ hipError_t launch_rows_form(const ScoreArgs &a, hipStream_t stream) {
 //   words 2,000, 60,000 rows: 282 -> 274 us; 2,000 rows 13.8 -> 12.5
 //   words 4,000, 60,000 rows: 561 -> 524 us; words 6,250, 32,768 rows: 480 -> 458
 //   words 8,300: 128 rows 9.1 -> 9.0 us (three chunks of U = 4 in flight, the form of more rows, 10.1);
-//                words 18,992: 512 rows 27.1 us either way (27.5), 8,192 rows 365 (357)
+//                words 18,992: 512 rows 25.9 us either way (26.7), 8,192 rows 365 (357)
+//   words 18,992, rows for half the CUs at most: 64 rows 12.4 us (sixteen wavefronts; eight 13.1, with three
+//                chunks in flight 12.8), 128 rows 13.3 (13.4, 13.6), and 11.3 (11.9, 11.5) and 11.8 (12.9, 12.2)
+//                where the last-level cache holds them; 160 rows 13.9 (13.8, 14.3).  Words 12,500, 64 rows
+//                9.9 (10.4, 11.1), but 10,500 9.5 (9.3, 9.9), and fp32 18,992 11.3 (11.0, 11.3)
 //   words 12,500, 80,000 rows: 2,368 -> 2,252 us (U = 8, one chunk at a time: 2,260)
 //   words 18,992: 128 rows 58 -> 11 us, 8,192 rows 383 -> 362 (sixteen wavefronts 366),
 //                 32,768 rows 1,444 -> 1,425 (eight 1,435), 174,554 rows 7,681 -> 7,637 (7,669),
@@ -609,6 +613,7 @@ hipError_t launch_rows(const ScoreArgs &a, hipStream_t stream) {
     }
     if (DT == STRIDE_BF16 && words < 1408) return launch_rows_form<DT, 4, 1, 4, 1>(a, stream);
     if (words < 3072) return launch_rows_form<DT, 4, 1, 8, 1>(a, stream);
+    if (DT == STRIDE_BF16 && words >= 12288 && items <= 128) return launch_rows_form<DT, 16, 1, 8, 1>(a, stream);
     if (words < 8192 || items < 4096) return launch_rows_form<DT, 8, 1, 8, 1>(a, stream);
     const bool lines = a.ld * Elem<DT>::kSize % 128 == 0;
     if (items >= 16384 && (DT == STRIDE_F32 ? words >= 8448 : (lines && words >= 16384 && words < 24576)))

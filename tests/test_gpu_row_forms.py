@@ -197,9 +197,12 @@ def test_masks_of_the_lowest_value(dtype, exact_kl):
         _masked(words, n, torch.bfloat16 if dtype == "bf16" else torch.float32, masked, exact_kl)
 
 
-# words, rows: both sides of the borders by the number of rows (1,024 or 2,048) and by the words (1,408)
+# words, rows: both sides of the borders by the number of rows (1,024 or 2,048, 128) and by the words (1,408,
+# 12,288)
 BORDERS = [(511, 1024), (511, 1025), (512, 1024), (512, 2048), (512, 2049), (1023, 2048), (1023, 2049),
-           (1024, 40), (1407, 300), (1408, 300), (3, 1024), (3, 1025)]
+           (1024, 40), (1407, 300), (1408, 300), (3, 1024), (3, 1025),
+           (12287, 128), (12288, 128), (12288, 129), (12289, 128), (18992, 9), (24577, 128),
+           (65537, 12)]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
