@@ -22,7 +22,7 @@ namespace {
 
 // Where the average rollout has at most 128 units, one wave takes each record of up to kWaveLength units
 // (two of its chunks of 512) and kHelpers workgroups of the same launch the longer ones: 40,000 units
-// before 1,500 rollouts of 3 took a wave 162 us and take a helper 23.8 (one workgroup of 256 for every
+// before 1,500 rollouts of 3 took a wave 161 us and take a helper 24.5 (one workgroup of 256 for every
 // rollout and two passes: 43.7).  A prime number of helpers, so that long rollouts at regular places are
 // spread over them.
 constexpr int64_t kWaveLength = 1024;
@@ -99,21 +99,21 @@ __device__ __forceinline__ void pick(const RestartArgs &a, int64_t r, const Reco
     VT v[PU], v2[PU];
     uint8_t mk[PU], mk2[PU];
     auto fetch = [&](int64_t c, VT *x, uint8_t *m) __attribute__((always_inline)) {
-        const VT *p = vals + first + c + tid;
-        if (c + (int64_t)NT * PU <= len) {  // a whole chunk: no load waits for another's bound
+        if (c >= len) return;
+        // Past the record's end its last unit is read again, so that no load waits for a bound, and the mask
+        // is looked for once for all: 64 records of 4,096 units with a mask 5.7 us (a branch for each load
+        // 6.0, and 6.3 where the records are ragged), 500,000 before 10,000 of 2 314 (the mask looked for at
+        // each load 494).
+        const int last = len - c > NT * PU ? NT * PU - 1 : (int)(len - c) - 1;
+        const VT *p = vals + first + c;
 #pragma unroll
-            for (int k = 0; k < PU; ++k) x[k] = p[k * NT];
-        } else {
-#pragma unroll
-            for (int k = 0; k < PU; ++k) x[k] = c + k * NT + tid < len ? p[k * NT] : (VT)0;
-        }
+        for (int k = 0; k < PU; ++k) x[k] = p[k * NT + tid < last ? k * NT + tid : last];
 #pragma unroll
         for (int k = 0; k < PU; ++k) m[k] = 1;
         if (a.mask) {
-            const uint8_t *q = a.mask + first + c + tid;
+            const uint8_t *q = a.mask + first + c;
 #pragma unroll
-            for (int k = 0; k < PU; ++k)
-                if (c + k * NT + tid < len) m[k] = q[k * NT];
+            for (int k = 0; k < PU; ++k) m[k] = q[k * NT + tid < last ? k * NT + tid : last];
         }
     };
     constexpr bool kAhead = NT > 256;  // the next chunk's values in flight while this one is looked at
@@ -197,9 +197,10 @@ __device__ __forceinline__ void pick(const RestartArgs &a, int64_t r, const Reco
 // values in flight: 5.4 us against 5.0 where 256 threads need no second chunk).  Latency bounds
 // the kernels (a chunk costs a round trip to memory and two barriers), and for many short rollouts
 // the number of workgroups.  Measured against 256 threads for every rollout and two passes:
-// 8 x 16,384 units 34.2 -> 16.2 us (1,024 threads 14.0, but 9.1 against 7.2 where the first chunk
-// ends the search), 64 x 4,096 11.6 -> 7.1, 8 x 8 4.6 -> 3.6, 20,000 x 12 37.9 -> 10.7,
-// 200,000 x 3 398 -> 83.
+// 8 x 16,384 units 28.1 -> 9.9 us with a mask and 24.3 -> 9.5 without (graph replays, the whole record
+// correct), 64 x 4,096 9.3 -> 5.7, 500 x 500 5.5 -> 4.5, 8 x 8 4.7 -> 3.6, 20,000 x 12 39.5 -> 10.7,
+// 200,000 x 3 392 -> 83.  1,024 threads are ahead at 8 x 16,384 and 1.9 us behind where the first chunk ends
+// the search.
 //
 // One wave per rollout, four to a workgroup, behind `helpers` workgroups that take the records of more
 // than kWaveLength units, which the waves pass over: helper k looks at rollouts k, k + helpers, ...
@@ -251,7 +252,12 @@ __global__ __launch_bounds__(NT) void restart_block_kernel(RestartArgs a) {
     const int64_t r = block_index<NT>();
     if (r >= a.L.n_rollouts) return;
     const Record rec = record_of(a, r, threadIdx.x == 0);
-    if (rec.len >= 0) pick<VT, NT, 8>(a, r, rec, threadIdx.x, &s_min, s_val, s_idx);
+    if (rec.len < 0) return;
+    // half the chunk where it holds the record: 300 records of 250 units or of 1,024 5.2 -> 4.4 us
+    if (NT == 256 && rec.len <= 4 * NT)
+        pick<VT, NT, 4>(a, r, rec, threadIdx.x, &s_min, s_val, s_idx);
+    else
+        pick<VT, NT, 8>(a, r, rec, threadIdx.x, &s_min, s_val, s_idx);
 }
 
 template <typename VT>

@@ -186,3 +186,40 @@ def test_one_long_rollout_among_short_ones_takes_its_own_time(call):
     alone, among = time([40000]), time([40000] + [3] * 1500)
     print(f"{call}, ms for 20 calls: alone {alone:.3f}, among short ones {among:.3f}", flush=True)
     assert among <= 2.5 * alone
+
+
+def test_a_record_that_does_not_fill_its_chunk():
+    """Restart pick of 64 records of 4,095 units with a mask, one less than a chunk: the time of 4,096."""
+    import torch
+    import paper_2609_14636_amd as P
+    graphs = []
+    for n in (4095, 4096):
+        U = 64 * n
+        lay = P.Layout(torch.arange(65, dtype=torch.int32, device="cuda"),
+                       torch.arange(0, U + 1, n, dtype=torch.int64, device="cuda"), U)
+        path = P.Path(lay, P.STRIDE_UNIT_TOKEN, with_student=False)
+        vals, mask = -torch.rand(U, device="cuda"), torch.ones(U, dtype=torch.uint8, device="cuda")
+
+        def run(lay=lay, vals=vals, mask=mask, path=path):
+            P.stride_restart_turn(lay, P.STRIDE_UNIT_TOKEN, vals, None, [-2.0], mask, path.k_star, path.k0,
+                                  path.k_max, path.flags)
+        run()
+        torch.cuda.synchronize()
+        assert path.k_max.tolist() == [n] * 64
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(50):
+                run()
+        graphs.append((graph, run))
+    best = [float("inf")] * 2
+    for _ in range(15):
+        for i in (0, 1):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            graphs[i][0].replay()
+            a.record()
+            graphs[i][0].replay()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) * 20)
+    print(f"us: 4,095 units {best[0]:.2f}, 4,096 units {best[1]:.2f}", flush=True)
+    assert best[0] <= 1.04 * best[1]   # a branch for each load: 1.06 and more
